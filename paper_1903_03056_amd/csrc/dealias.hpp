@@ -204,9 +204,8 @@ hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T
     ga.ncls = ncls;
     ga.nrho = inner.nrho;
     ga.nb = nb;
-    const int64_t groups = ((nb + 7) / 8) * 8 * int64_t(ncls) * inner.nrho * CH;
     gain_kernel<T, NI, CH, CZ, PIPE, false, GAIN_COMPLEX>
-        <<<dim3(unsigned(groups)), dim3(GainK<T, NI, CH, CZ>::NT), 0, st>>>(ga);
+        <<<dim3(gain_groups(nb, int64_t(ncls) * inner.nrho * CH)), dim3(GainK<T, NI, CH, CZ>::NT), 0, st>>>(ga);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     mark(2);
 

@@ -549,21 +549,15 @@ union alignas(16) Smem {
     cx<float> buf[GainK<float, N, 2, 1>::LDS];
 };
 
-// Work items are dealt to the 8 XCDs round-robin; on one XCD, the items of NG nodes
-// (b, b + 8, ...) run interleaved, same item next to each other, so that the nodes'
-// prepared inputs and the item's shift tables are read from that XCD's L2.
+// The items of NG nodes of an XCD run interleaved (gain_item), so that the nodes' prepared
+// inputs and the item's shift tables are read from that XCD's L2.
 constexpr int NG = 4;
 
 __global__ __launch_bounds__(NT) void gain_kernel(Args a) {
     __shared__ Smem sm;
     Lds& L = sm.m;
-    const int ipn = a.ncls * a.nrho * 2;
-    const int gi = blockIdx.x;
-    const int xcd = gi & 7, local = gi >> 3;
-    const int grp = local / (ipn * NG), rem = local % (ipn * NG);
-    const int b = (grp * NG + rem % NG) * 8 + xcd;
-    if (b >= a.nb) return;
-    int item = rem / NG;
+    int b, item;
+    if (!gain_item<NG>(blockIdx.x, a.nb, a.ncls * a.nrho * 2, b, item)) return;
     const int c = item % 2;
     item /= 2;
     const int q = item % a.nrho;
@@ -644,8 +638,7 @@ hipError_t launch_gain_mfma32(const dgfs_plan& p, const float* f, cx<float>* P, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t ipn = int64_t(a.ncls) * p.nrho * 2;
-    const int64_t groups = ((nb + 8 * mfma::NG - 1) / (8 * mfma::NG)) * 8 * mfma::NG * ipn;
-    mfma::gain_kernel<<<dim3(unsigned(groups)), dim3(mfma::NT), 0, st>>>(a);
+    mfma::gain_kernel<<<dim3(gain_groups(nb, ipn)), dim3(mfma::NT), 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,36 @@
+"""How the gain's work items are dealt to the chip: whole nodes per XCD for every eight
+nodes, the items of the last nb % 8 nodes over all XCDs.  At the edges of that rule every
+node's result is its result alone, bit for bit, and the oracle's.
+
+Tolerances: relative L-inf over each (node, species) against the FP64 oracle, 1e-12 for
+FP64 and 1e-5 for FP32 plans, as in the other parity tests."""
+import numpy as np
+import pytest
+
+from oracle import spectral as OS
+from synth import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("N,precision", [(16, "f64"), (24, "f32"), (32, "f32")])
+@pytest.mark.parametrize("batch", [1, 7, 8, 9, 39])
+def test_every_node_at_the_edges_of_the_dealing(N, precision, batch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_03056_amd import CollisionPlan
+    print(f"[case] gain items N={N} {precision} batch {batch}", flush=True)
+    masses, L, M, nrho = (1.0, 2.0), 6.0, 6, 3
+    plan = CollisionPlan(masses, N, L, M, nrho, omega=0.74, precision=precision)
+    f = I.draw_bimaxwellian_batch(np.random.default_rng(61), batch, 2, N, L, masses, noise=1e-2)
+    ft = torch.tensor(f, dtype=plan.dtype, device="cuda")
+    Q = plan.collide(ft)
+    for b in range(batch):
+        assert torch.equal(plan.collide(ft[b:b + 1].contiguous())[0], Q[b]), b
+    ref = OS.collide(ft[batch - 1].double().cpu().numpy(), OS.vhs_problem(masses, 0.74, L, N, M, nrho))
+    got = Q[batch - 1].double().cpu().numpy()
+    err = float(np.max(np.abs(got - ref).reshape(2, -1).max(1) / np.abs(ref).reshape(2, -1).max(1)))
+    print(f"relative L-inf {err:.3e}", flush=True)
+    assert err <= (1e-12 if precision == "f64" else 1e-5)
