@@ -183,7 +183,7 @@ hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T
     hipError_t e;
 
     mark(0);
-    if ((e = fft3d<T, N>(fN, f, int64_t(nb) * s, -1, T(1.0 / double(N3)), st)) != hipSuccess) return e;
+    if ((e = fft3d_forward<T, N>(fN, f, int64_t(nb) * s, T(1.0 / double(N3)), st)) != hipSuccess) return e;
     pad_kernel<T, N, NI><<<blocks_for(int64_t(nb) * s * NI3), 256, 0, st>>>(fN, fhI, int64_t(nb) * s);
     if ((e = hipMemcpyAsync(fI, fhI, sizeof(cx<T>) * nb * s * NI3, hipMemcpyDeviceToDevice, st)) != hipSuccess)
         return e;

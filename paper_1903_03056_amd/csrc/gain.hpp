@@ -1400,25 +1400,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void r
 
 // ====================================================== inverse transform + combine
 // The inverse transform of the gain and loss spectra (Hermitian, the k_z <= N/2 half
-// stored): the x- and y-passes run on the half in place (half_pass_kernel); the z-pass
-// restores each row's conjugate half, transforms it and keeps the real part, fused with
-// the combination Q = g - f_i l of the slot's species i (zpass_combine_kernel).
-template <typename T, int N, int AXIS>
-__global__ __launch_bounds__(256) void half_pass_kernel(cx<T>* data, int64_t npencils) {
+// stored): the x-pass runs on the half in place (half_xpass_kernel); the y-pass and the
+// z-pass, which restores each row's conjugate half and keeps the real part, run on one
+// x-plane after the other through LDS, fused with the combination Q = g - f_i l of the
+// slot's species i (inverse_yz_kernel).
+template <typename T, int N>
+__global__ __launch_bounds__(256) void half_xpass_kernel(cx<T>* data, int64_t npencils) {
     constexpr int KZH = N / 2 + 1;
-    constexpr int64_t NH = int64_t(N) * N * KZH;
+    constexpr int64_t NH = int64_t(N) * N * KZH, stride = int64_t(N) * KZH;
     const int64_t pid = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (pid >= npencils) return;
     const int64_t field = pid / (N * KZH);
-    const int r = int(pid - field * (N * KZH));
-    int64_t base, stride;
-    if constexpr (AXIS == 0) {  // r = (k_y, k_z)
-        base = field * NH + r;
-        stride = int64_t(N) * KZH;
-    } else {                    // r = (x, k_z)
-        base = field * NH + int64_t(r / KZH) * (N * KZH) + (r % KZH);
-        stride = KZH;
-    }
+    const int64_t base = field * NH + (pid - field * (N * KZH));
     cx<T> v[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) v[k] = data[base + k * stride];
@@ -1427,22 +1420,50 @@ __global__ __launch_bounds__(256) void half_pass_kernel(cx<T>* data, int64_t npe
     for (int k = 0; k < N; ++k) data[base + k * stride] = v[k];
 }
 
+// PL x-planes of a slot to a workgroup: 2 PL KZH columns of both spectra, then PL N rows,
+// on about as many threads, a few workgroups to a CU.  With the y- and z-passes as two launches 512 FP32
+// slots at N = 32 took 50 + 57 us, together 59; one FP64 node at N = 16 10.0 us, now 4.7.
+template <int N>
+struct InverseTile {
+    static constexpr int PL = N <= 16 ? 3 : N == 24 ? 2 : N == 32 ? 3 : 1;
+    static constexpr int KZH = N / 2 + 1;   // odd for every N here: rows of KZH values spread over the banks
+    static constexpr int NT = (2 * PL * KZH + 63) / 64 * 64;
+};
+
 template <typename T, int N>
-__global__ __launch_bounds__(256) void zpass_combine_kernel(const cx<T>* __restrict__ Gh,
-                                                            const cx<T>* __restrict__ Lh, const T* __restrict__ f,
-                                                            T* __restrict__ Q, const int* __restrict__ slots,
-                                                            int nslots, int s, int64_t nrows) {
-    constexpr int KZH = N / 2 + 1;
+__global__ __launch_bounds__(InverseTile<N>::NT) void inverse_yz_kernel(const cx<T>* __restrict__ Gh,
+                                                                        const cx<T>* __restrict__ Lh,
+                                                                        const T* __restrict__ f, T* __restrict__ Q,
+                                                                        const int* __restrict__ slots, int nslots,
+                                                                        int s, int64_t nplanes) {
+    using K = InverseTile<N>;
+    constexpr int KZH = K::KZH;
     constexpr int64_t N2 = int64_t(N) * N, N3 = N2 * N;
-    const int64_t row = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (row >= nrows) return;
-    const int64_t bs = row / N2;         // (node, slot)
-    const int64_t xy = row - bs * N2;
-    const int slot = int(bs % nslots);
+    __shared__ cx<T> buf[2][K::PL][N * KZH];
+    const int t = threadIdx.x;
+    const int64_t p0 = int64_t(blockIdx.x) * K::PL;
+    if (t < 2 * K::PL * KZH) {
+        const int fld = t / (K::PL * KZH), pl = t / KZH % K::PL, kz = t % KZH;
+        if (p0 + pl < nplanes) {
+            const cx<T>* src = (fld == 0 ? Gh : Lh) + (p0 + pl) * (N * KZH) + kz;
+            cx<T> v[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = src[k * KZH];
+            fft<N, +1>(v);
+#pragma unroll
+            for (int k = 0; k < N; ++k) buf[fld][pl][k * KZH + kz] = v[k];
+        }
+    }
+    __syncthreads();
+    const int pl = t / N, y = t % N;
+    const int64_t plane = p0 + pl;       // (node, slot, x)
+    if (pl >= K::PL || plane >= nplanes) return;
+    const int64_t bs = plane / N;
+    const int64_t xy = (plane - bs * N) * N + y;
+    const int sp = slots[5 * int(bs % nslots)];
     const int64_t b = bs / nslots;
-    const int sp = slots[5 * slot];
-    const cx<T>* g = Gh + row * KZH;
-    const cx<T>* l = Lh + row * KZH;
+    const cx<T>* g = &buf[0][pl][y * KZH];
+    const cx<T>* l = &buf[1][pl][y * KZH];
     cx<T> vg[N], vl[N];
 #pragma unroll
     for (int k = 0; k < KZH; ++k) {
@@ -1504,7 +1525,7 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
 
     const char* dev = static_cast<const char*>(p.dev);
     mark(0);
-    hipError_t e = fft3d<T, N>(fhat, f, int64_t(nb) * p.s, -1, T(1.0 / double(N3)), st);
+    hipError_t e = fft3d_forward<T, N>(fhat, f, int64_t(nb) * p.s, T(1.0 / double(N3)), st);
     if (e != hipSuccess) return e;
     mark(1);
 
@@ -1581,15 +1602,15 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
 
     {
         const int64_t np = 2 * int64_t(nb) * ss.nslots * N * (N / 2 + 1);
-        half_pass_kernel<T, N, 0><<<dim3(unsigned((np + 255) / 256)), dim3(256), 0, st>>>(Gt, np);
-        half_pass_kernel<T, N, 1><<<dim3(unsigned((np + 255) / 256)), dim3(256), 0, st>>>(Gt, np);
+        half_xpass_kernel<T, N><<<dim3(unsigned((np + 255) / 256)), dim3(256), 0, st>>>(Gt, np);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     mark(4);
 
-    const int64_t rows = int64_t(nb) * ss.nslots * N * N;
-    zpass_combine_kernel<T, N><<<dim3(unsigned((rows + 255) / 256)), dim3(256), 0, st>>>(
-        Gt, Lt, f, Q, ra.slots, ss.nslots, p.s, rows);
+    const int64_t planes = int64_t(nb) * ss.nslots * N;
+    constexpr int IPL = InverseTile<N>::PL;
+    inverse_yz_kernel<T, N><<<dim3(unsigned((planes + IPL - 1) / IPL)), dim3(InverseTile<N>::NT), 0, st>>>(
+        Gt, Lt, f, Q, ra.slots, ss.nslots, p.s, planes);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     mark(5);
     return hipSuccess;
