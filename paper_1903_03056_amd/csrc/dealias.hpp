@@ -157,7 +157,7 @@ inline unsigned blocks_for(int64_t n) { return unsigned((n + 255) / 256); }
 
 // outer: the N-grid plan (conservation tables, slots); inner: its NI = 3N/2 companion
 // (phases, kernel-mode and loss tables, classes, slots of the NI grid).
-template <typename T, int N, int CH, int CZ, bool PIPE>
+template <typename T, int N, int CH, int CZ>
 hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T* f, T* Q, int nb, void* ws,
                          bool pairs, hipStream_t st, hipEvent_t* ev) {
     constexpr int NI = 3 * N / 2;
@@ -204,7 +204,7 @@ hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T
     ga.ncls = ncls;
     ga.nrho = inner.nrho;
     ga.nb = nb;
-    gain_kernel<T, NI, CH, CZ, PIPE, false, GAIN_COMPLEX>
+    gain_kernel<T, NI, CH, CZ, PIPE_OFF, false, GAIN_COMPLEX>
         <<<dim3(gain_groups(nb, int64_t(ncls) * inner.nrho * CH)), dim3(GainK<T, NI, CH, CZ>::NT), 0, st>>>(ga);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     mark(2);

@@ -10,13 +10,13 @@ hipError_t run_dealias_24(const dgfs_plan& outer, const dgfs_plan& inner, const 
     const int key = inner.geo.CH * 100 + inner.geo.CZ;
     if (outer.precision == DGFS_FP64) {
         switch (key) {
-            case 604: return detail::run_dealiased<double, 24, 6, 4, false>(
+            case 604: return detail::run_dealiased<double, 24, 6, 4>(
                 outer, inner, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-        case 302: return detail::run_dealiased<float, 24, 3, 2, false>(
+        case 302: return detail::run_dealiased<float, 24, 3, 2>(
             outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }

@@ -11,13 +11,13 @@ hipError_t run_dealias_48(const dgfs_plan& outer, const dgfs_plan& inner, const 
     const int key = inner.geo.CH * 100 + inner.geo.CZ;
     if (outer.precision == DGFS_FP64) {
         switch (key) {
-            case 7208: return detail::run_dealiased<double, 48, 72, 8, false>(
+            case 7208: return detail::run_dealiased<double, 48, 72, 8>(
                 outer, inner, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-        case 2404: return detail::run_dealiased<float, 48, 24, 4, false>(
+        case 2404: return detail::run_dealiased<float, 48, 24, 4>(
             outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }

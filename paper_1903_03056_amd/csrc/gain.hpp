@@ -28,6 +28,16 @@ namespace dgfs {
 //               to those planes (sums with (-1)^x, (-1)^y, (-1)^z) and stored.
 enum { GAIN_REAL = 0, GAIN_COMPLEX = 1, GAIN_VSS = 2 };
 
+// How the x-pass issues the loads of the next sub-sequence while it combines the current
+// one, chosen per geometry by measurement (tiles_<N>.hip, vss_<N>.hip): not at all, in a
+// buffer that is copied at every step, or in two buffers in turn (no copies, more registers
+// alive).  The packed form takes any value but PIPE_OFF as two buffers.  FP64 gains, ms
+// off / rotating / two: N = 16 (200 nodes) 0.527 / 0.442 / 0.427, N = 24 (60) 2.03 / 2.28 /
+// 2.14, N = 32 (32) 3.91 / 3.15 / 3.33, N = 48 (4) 3.62 / 3.02 / 2.93, N = 64 (1) 6.49 / 5.65
+// / 5.59: the 16-byte loads leave few in flight otherwise; at N = 24 the registers cost a
+// wavefront.
+enum { PIPE_OFF = 0, PIPE_ROTATE = 1, PIPE_TWO = 2 };
+
 // Geometry of one work item: the x-chunk c (x-indices = c mod CH, NP = N/CH of them)
 // of one S_q field.  Each y/z pencil of the chunk is shared by CZ thread groups: group
 // cz keeps the outputs with index = cz mod CZ (decimation in frequency), so a thread
@@ -235,8 +245,8 @@ __device__ __forceinline__ bool pencil_slot(int slot, int& ly, int& lz) {
 // sum_t of the chunk terms in[l + t NP] * kx[l + t NP] for one pencil, with two load
 // buffers in turn: the next batch of NP loads is in flight while the other is consumed,
 // and no register copies between batches.  U tables (one per output) share the loads.
-// (The packed N = 48 form's x-pass; at N = 32 the one-field x-pass keeps its rotating
-// buffer, which compiles without spills there.)
+// (In FP32 at N = 32 the one-field x-pass keeps its rotating buffer, which compiles without
+// spills there.)
 template <typename T, int NP, int CH, int U>
 __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, int rs_stride,
                                            const cx<T>* const (&kx)[U], cx<T>* const (&y)[U]) {
@@ -274,8 +284,8 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
 // over (l_y, l_z)) and keeps only the chunk's x-outputs: the CH strided input
 // sub-sequences are combined with kxt, which carries the x-phase, the split factor
 // e^{2 pi i t c / CH} and the twiddle e^{2 pi i l c / N}.  The y- and z-phases are
-// constant along an x-pencil and multiply its outputs.  With PIPE the loads of the
-// next sub-sequence are issued before the current one is combined.
+// constant along an x-pencil and multiply its outputs.  With PIPE != PIPE_OFF the loads of
+// the next sub-sequence are issued before the current one is combined.
 //
 // f is real, so f_hat(l_x, -P) = conj(f_hat(-l_x, P)); with the linear x-phase this
 // gives, for every output x-index n, G(-P)[n] = conj(G(P)[n] + delta_P (-1)^n) where
@@ -295,7 +305,7 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
 // x-pencils are transformed, from 2/3 of their inputs, and stored with their own y/z phase;
 // the y- and z-passes skip the zero rows and columns.  (Ten FP32 nodes padded to 48^3, whole call: every
 // pencil transformed 4.04 ms, the kept ones 2.14 ms; two load buffers in turn: no change.)
-template <typename T, int N, int CH, int CZ, bool PIPE, bool HERM = true>
+template <typename T, int N, int CH, int CZ, int PIPE, bool HERM = true>
 __device__ __forceinline__ void field_ifft(const cx<T>* __restrict__ fh, const cx<T>* __restrict__ kxt,
                                            const cx<T>* __restrict__ yzt, T nyq, int c, cx<T>* buf, int cz,
                                            int m, int r, cx<T>* out) {
@@ -368,7 +378,11 @@ __device__ __forceinline__ void field_ifft(const cx<T>* __restrict__ fh, const c
                 for (int l = 0; l < K::NP; ++l)
                     cmac(y[l], cx<T>{a[l].x - mk * b[l].y, a[l].y + mk * b[l].x}, kxt[l + t * K::NP]);
             }
-        } else if constexpr (PIPE) {
+        } else if constexpr (PIPE == PIPE_TWO) {
+            const cx<T>* const kx1[1] = {kxt};
+            cx<T>* const y1[1] = {y};
+            x_sum_pipe<T, K::NP, CH, 1>(rs, vo, RS, kx1, y1);
+        } else if constexpr (PIPE == PIPE_ROTATE) {
             cx<T> nxt[K::NP];
 #pragma unroll
             for (int l = 0; l < K::NP; ++l) nxt[l] = bload<T>(rs, vo, l * RS);
@@ -441,7 +455,7 @@ constexpr bool pack_ok() {
 
 // The chunk x-transform of one pencil P of one field (with SELF in a wavefront holding
 // self-paired slots: of f(., P) + i mk f(., P + N/2), both loads of an index together).
-template <typename T, int N, int CH, bool PIPE>
+template <typename T, int N, int CH, int PIPE>
 __device__ __forceinline__ void x_pencil(__amdgpu_buffer_rsrc_t rs, int vo, int vo2, T mk, bool two,
                                          const cx<T>* __restrict__ kxt, cx<T>* y) {
     constexpr int NP = N / CH;
@@ -478,7 +492,7 @@ __device__ __forceinline__ void x_pencil(__amdgpu_buffer_rsrc_t rs, int vo, int 
 // x_pencil for two fields with the same spectrum (a like class: A and B both shift f^i)
 // on a paired slot: every input is loaded once and enters both sums, each with its own
 // phase table; each output takes the same operations in the same order as x_pencil's.
-template <typename T, int N, int CH, bool PIPE>
+template <typename T, int N, int CH, int PIPE>
 __device__ __forceinline__ void x_pencil2(__amdgpu_buffer_rsrc_t rs, int vo, const cx<T>* __restrict__ kxa,
                                           const cx<T>* __restrict__ kxb, cx<T>* ya, cx<T>* yb) {
     constexpr int NP = N / CH;
@@ -572,7 +586,7 @@ __device__ __forceinline__ cx<T> pack_nconj(cx<T> a, cx<T> b) { return cx<T>{-a.
 // (1-D transforms along the other index).  Their transforms are purely imaginary, i alpha,
 // so the pieces of A and B are packed the same way: E = i alpha_A - alpha_B.  Then
 // Re(A B) = a b - alpha_A alpha_B = Re Z Im Z + Re E Im E.
-template <typename T, int N, int CH, int CZ, bool PIPE>
+template <typename T, int N, int CH, int CZ, int PIPE>
 __device__ __forceinline__ void packed_direction(const cx<T>* __restrict__ fa, const cx<T>* __restrict__ fb,
                                                  const cx<T>* __restrict__ kxa, const cx<T>* __restrict__ yza,
                                                  T nyqa, const cx<T>* __restrict__ kxb,
@@ -836,7 +850,7 @@ __device__ __forceinline__ void store_partial(cx<T>* buf, cx<T>* Pq, int c) {
     }
 }
 
-template <typename T, int N, int CH, int CZ, bool PIPE, bool PACK, int MODE>
+template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, int MODE>
 __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArgs<T> a) {
     using K = GainK<T, N, CH, CZ>;
     constexpr bool CPLX = MODE != GAIN_REAL;  // the whole spectrum of a complex field is stored
@@ -1495,7 +1509,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // ev (optional): 6 events recorded at the stage boundaries (start, after forward FFT,
 // after gain, after radial, after the inverse x/y passes, after the z-pass + combine).
 // MF: the gain stage runs on the matrix cores (FP32, N = 32, VHS only).
-template <typename T, int N, int CH, int CZ, bool PIPE, bool PACK, bool VSS, bool MF = false>
+template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, bool VSS, bool MF = false>
 hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, bool pairs, hipStream_t st,
                      hipEvent_t* ev) {
     static_assert(!MF || (std::is_same_v<T, float> && N == 32 && CH == 2 && !VSS), "matrix-core gain: FP32 VHS N = 32");

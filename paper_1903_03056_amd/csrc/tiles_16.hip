@@ -10,17 +10,17 @@ hipError_t run_tiles_16(const dgfs_plan& p, const void* f, void* Q, int nb, void
     const int key = p.geo.CH * 100 + p.geo.CZ;
     if (p.precision == DGFS_FP64) {
         switch (key) {
-            case 101: return detail::run_slice<double, 16, 1, 1, false, false, false>(
+            case 101: return detail::run_slice<double, 16, 1, 1, PIPE_TWO, false, false>(
                 p, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-        case 201: return detail::run_slice<float, 16, 2, 1, false, false, false>(
+        case 201: return detail::run_slice<float, 16, 2, 1, PIPE_OFF, false, false>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 101: return detail::run_slice<float, 16, 1, 1, false, false, false>(
+        case 101: return detail::run_slice<float, 16, 1, 1, PIPE_OFF, false, false>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 102: return detail::run_slice<float, 16, 1, 2, false, false, false>(
+        case 102: return detail::run_slice<float, 16, 1, 2, PIPE_OFF, false, false>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }

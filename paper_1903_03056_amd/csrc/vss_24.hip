@@ -10,17 +10,17 @@ hipError_t run_vss_24(const dgfs_plan& p, const void* f, void* Q, int nb, void* 
     const int key = p.geo.CH * 100 + p.geo.CZ;
     if (p.precision == DGFS_FP64) {
         switch (key) {
-            case 302: return detail::run_slice<double, 24, 3, 2, false, false, true>(
+            case 302: return detail::run_slice<double, 24, 3, 2, PIPE_OFF, false, true>(
                 p, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-        case 301: return detail::run_slice<float, 24, 3, 1, false, false, true>(
+        case 301: return detail::run_slice<float, 24, 3, 1, PIPE_OFF, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 302: return detail::run_slice<float, 24, 3, 2, false, false, true>(
+        case 302: return detail::run_slice<float, 24, 3, 2, PIPE_OFF, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 304: return detail::run_slice<float, 24, 3, 4, false, false, true>(
+        case 304: return detail::run_slice<float, 24, 3, 4, PIPE_OFF, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }
@@ -33,17 +33,17 @@ hipError_t run_dealias_16(const dgfs_plan& outer, const dgfs_plan& inner, const 
     const int key = inner.geo.CH * 100 + inner.geo.CZ;
     if (outer.precision == DGFS_FP64) {
         switch (key) {
-            case 302: return detail::run_dealiased<double, 16, 3, 2, false>(
+            case 302: return detail::run_dealiased<double, 16, 3, 2>(
                 outer, inner, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-            case 301: return detail::run_dealiased<float, 16, 3, 1, false>(
+            case 301: return detail::run_dealiased<float, 16, 3, 1>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-            case 302: return detail::run_dealiased<float, 16, 3, 2, false>(
+            case 302: return detail::run_dealiased<float, 16, 3, 2>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-            case 304: return detail::run_dealiased<float, 16, 3, 4, false>(
+            case 304: return detail::run_dealiased<float, 16, 3, 4>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }

@@ -10,17 +10,17 @@ hipError_t run_vss_48(const dgfs_plan& p, const void* f, void* Q, int nb, void* 
     const int key = p.geo.CH * 100 + p.geo.CZ;
     if (p.precision == DGFS_FP64) {
         switch (key) {
-            case 1204: return detail::run_slice<double, 48, 12, 4, false, false, true>(
+            case 1204: return detail::run_slice<double, 48, 12, 4, PIPE_TWO, false, true>(
                 p, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-        case 602: return detail::run_slice<float, 48, 6, 2, true, false, true>(
+        case 602: return detail::run_slice<float, 48, 6, 2, PIPE_ROTATE, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 1204: return detail::run_slice<float, 48, 12, 4, false, false, true>(
+        case 1204: return detail::run_slice<float, 48, 12, 4, PIPE_OFF, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-        case 1202: return detail::run_slice<float, 48, 12, 2, false, false, true>(
+        case 1202: return detail::run_slice<float, 48, 12, 2, PIPE_OFF, false, true>(
             p, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }
@@ -33,17 +33,17 @@ hipError_t run_dealias_32(const dgfs_plan& outer, const dgfs_plan& inner, const 
     const int key = inner.geo.CH * 100 + inner.geo.CZ;
     if (outer.precision == DGFS_FP64) {
         switch (key) {
-            case 1204: return detail::run_dealiased<double, 32, 12, 4, false>(
+            case 1204: return detail::run_dealiased<double, 32, 12, 4>(
                 outer, inner, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (key) {
-            case 602: return detail::run_dealiased<float, 32, 6, 2, true>(
+            case 602: return detail::run_dealiased<float, 32, 6, 2>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-            case 1204: return detail::run_dealiased<float, 32, 12, 4, false>(
+            case 1204: return detail::run_dealiased<float, 32, 12, 4>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
-            case 1202: return detail::run_dealiased<float, 32, 12, 2, false>(
+            case 1202: return detail::run_dealiased<float, 32, 12, 2>(
                 outer, inner, static_cast<const float*>(f), static_cast<float*>(Q), nb, ws, pairs, st, ev);
         default: return hipErrorInvalidValue;
     }
