@@ -1100,13 +1100,33 @@ struct RadialArgs {
 // VSS: each class (up to two directions) partial is the whole spectrum Z of
 // Re S_0 + i Re S_1; the thread reads Z at k and -k and adds the Nyquist-plane terms
 // (vss_accumulate).
-template <typename T, int N, int CH, bool VSS>
+//
+// QS threads share an element: thread group g of the workgroup sums the radial points
+// q = g mod QS, the partial sums meet in LDS, and each group finishes the x-modes
+// j = g mod QS.  A small call has few elements (one FP64 node at N = 64: 8448 threads for
+// QS = 1, 1.15 ms in the latency of 64 dependent rounds of 32 loads each, 0.28 ms for
+// QS = 8; three N = 24 nodes 20 -> 10 us, one FP64 node at N = 16 8.3 -> 4.9 us, both with
+// QS = 4).  At large batches the kernel is bound by memory either way, and the shorter runs of
+// consecutive elements cost it a little (256 nodes at N = 32: 0.562 ms for QS = 1, 0.598 for
+// 4; 63 nodes at N = 24: 39 and 40 us; 50 heavy/light nodes at N = 48: 0.603 and 0.606 ms),
+// so N = 32, with two or four chunks and the largest batches, keeps QS = 1.
+// QS depends on N alone, so that a node's sums do not depend on the batch.
+template <int N>
+constexpr int radial_qs() { return N == 64 ? 8 : N == 32 ? 1 : 4; }
+
+template <typename T, int N, int CH, bool VSS, int QS>
 __global__ __launch_bounds__(256) void radial_kernel(RadialArgs<T> a) {
+    static_assert(!VSS || QS == 1, "the shared form covers the VHS sum");
     constexpr int NP = N / CH;
     constexpr int KZH = N / 2 + 1;
+    constexpr int EL = 256 / QS;   // elements of a workgroup
     constexpr int64_t N2 = int64_t(N) * N, N3 = N2 * N, PCH = int64_t(NP) * N * KZH;
-    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= int64_t(a.nb) * a.nslots * PCH) return;
+    __shared__ cx<double> part[QS > 1 ? QS : 1][QS > 1 ? CH : 1][QS > 1 ? EL : 1];
+    const int g = int(threadIdx.x) / EL, el = int(threadIdx.x) % EL;
+    int64_t t = int64_t(blockIdx.x) * EL + el;
+    const bool act = t < int64_t(a.nb) * a.nslots * PCH;
+    if (QS == 1 && !act) return;
+    if (!act) t = 0;   // shares the barrier and stores nothing
     const int e = int(t % PCH);
     const int64_t bs = t / PCH;
     const int slot = int(bs % a.nslots);
@@ -1181,7 +1201,7 @@ __global__ __launch_bounds__(256) void radial_kernel(RadialArgs<T> a) {
         const int cl = a.gterms[2 * (g0 + gi)], ft = a.gterms[2 * (g0 + gi) + 1];
         const cx<T>* Pb = a.P + (int64_t(b) * a.ncls + cl) * a.nrho * (CH * PCH) + e;
         const T* Ft = a.F + int64_t(ft) * a.nrho * a.K2;
-        for (int q = 0; q < a.nrho; ++q) {
+        for (int q = g; q < a.nrho; q += QS) {
             // the last radix-CH step of the x-transform (decimation in time): with
             // k_x = k_xp + j N/CH, DFT(S)(k_x) = sum_c (e^{-2 pi i kxp c / N} P_c) e^{-2 pi i j c / CH}
             cx<T> y[CH];
@@ -1199,27 +1219,35 @@ __global__ __launch_bounds__(256) void radial_kernel(RadialArgs<T> a) {
             }
         }
     }
-    cx<T> lac[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) lac[j] = cx<T>{T(0), T(0)};
-    for (int li = 0; li < nl; ++li) {
-        const int sj = a.lterms[2 * (l0 + li)], gt = a.lterms[2 * (l0 + li) + 1];
-        const cx<T>* fj = a.fhat + (int64_t(b) * a.s + sj) * N3 + ky * N + kz;
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int kx = kxp + j * NP;
-            const T gm = a.G[int64_t(gt) * a.K2 + k2[j]];
-            const cx<T> v = fj[kx * N2];
-            lac[j].x = fma(gm, v.x, lac[j].x);
-            lac[j].y = fma(gm, v.y, lac[j].y);
-        }
-    }
     const int64_t ob = (int64_t(b) * a.nslots + slot) * (N2 * KZH);
+    auto store = [&](int j, cx<double> sum) {
+        const int kx = kxp + j * NP;
+        cx<T> lac{T(0), T(0)};
+        for (int li = 0; li < nl; ++li) {
+            const int sj = a.lterms[2 * (l0 + li)], gt = a.lterms[2 * (l0 + li) + 1];
+            const T gm = a.G[int64_t(gt) * a.K2 + sq(kx) + kyz2];
+            const cx<T> v = a.fhat[(int64_t(b) * a.s + sj) * N3 + kx * N2 + ky * N + kz];
+            lac.x = fma(gm, v.x, lac.x);
+            lac.y = fma(gm, v.y, lac.y);
+        }
+        const int64_t o = ob + (int64_t(kx) * N + ky) * KZH + kz;
+        a.Gt[o] = cx<T>{T(sum.x), T(sum.y)};
+        a.Lt[o] = lac;
+    };
+    if constexpr (QS == 1) {
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const int64_t o = ob + (int64_t(kxp + j * NP) * N + ky) * KZH + kz;
-        a.Gt[o] = cx<T>{T(acc[j].x), T(acc[j].y)};
-        a.Lt[o] = lac[j];
+        for (int j = 0; j < CH; ++j) store(j, acc[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) part[g][j][el] = acc[j];
+        __syncthreads();
+        if (!act) return;
+        for (int j = g; j < CH; j += QS) {
+            cx<double> sum = part[0][j][el];
+#pragma unroll
+            for (int u = 1; u < QS; ++u) sum = sum + part[u][j][el];
+            store(j, sum);
+        }
     }
 }
 
@@ -1246,13 +1274,41 @@ __device__ __forceinline__ void mirror_paired_row(int r, int& kxp, int& ky) {
 // VSS radial sum with every slot of NB nodes in one thread: per class (up to two
 // directions), use and radial point the table values are loaded once and applied to the
 // NB nodes' partials (read at k and -k; the second use of an unlike class finds them in
-// L2).  The per-slot
-// accumulators are indexed with compile-time slots (SMAX >= nslots) under uniform
-// compares, so they stay in registers.  They are of the plan precision (FP32 plans sum in
-// FP32): that halves their registers and lets three waves share a SIMD, which is what
-// this latency-bound kernel needs.  Loss terms and outputs as in radial_kernel.
+// L2).  The per-slot accumulators are indexed with compile-time slots (SMAX >= nslots) under
+// uniform compares, so they stay in registers.  They are of the plan precision (FP32 plans
+// sum in FP32): that halves their registers.  Loss terms and outputs as in radial_kernel.
+// A node's arithmetic is the same for every NB.
+//
+// Large calls are bound by memory and want the tables shared by as many nodes as three
+// wavefronts per SIMD allow; small ones are bound by the latency of ncls nrho dependent
+// rounds of loads and want threads (vss_nodes).  At N = 32, FP32 (two chunks), ms for NB =
+// 1 / 2 / 3 / 4: 3 nodes 0.32 / 0.48 / 0.64 / 0.64, 10 nodes 0.44 / 0.53 / 0.70 / 0.88, 32
+// nodes 1.03 / 0.87 / 0.83 / 1.00, 96 nodes 2.56 / 1.97 / 1.84 / 2.09 (816 workgroups of NB
+// = 4 are 1.06 rounds), 256 nodes 6.7 / 4.8 / 4.3 / 3.95.  With three chunks (N = 24) one
+// node a thread is the fastest (40 nodes 0.46 / 0.52 / - / 0.87).
+// WPE, the wavefronts per SIMD asked of the compiler: three where the registers allow it
+// (up to two chunks in FP32), else what they do: N = 24 spilled for three (40 nodes, NB = 4,
+// 1.82 ms, for two 0.87), and so did FP64 (20 nodes at N = 32 10.6 ms; for one, NB = 2, 1.17).
+template <typename T, int CH>
+constexpr int vss_wpe() { return sizeof(T) == 8 ? 1 : CH <= 2 ? 3 : 2; }
+// Nodes per thread: one while that does not fill the chip's SIMDs with three wavefronts each
+// (FP64: one and a half), four from twice that many wavefronts of four (with one chunk, whose
+// registers are fewer, from two thirds of that: N = 16, 300 nodes of three species 2.87 ms a
+// call for two, 2.79 for four; 100 nodes of two 0.18 and 0.30 ms in the kernel), between them
+// two or three; fewer where the accumulators (NB x SMAX x CH) would not fit.
+template <typename T, int CH, int SMAX>
+constexpr int vss_nb_max() { return sizeof(T) == 8 ? (CH <= 4 && SMAX == 2 ? 2 : 1) : CH >= 3 ? 1 : 8 / (CH * SMAX) >= 2 ? 4 : 2; }
+template <typename T, int CH, int SMAX>
+int vss_nodes(int64_t nb, int64_t blocks_per_node) {
+    constexpr int most = vss_nb_max<T, CH, SMAX>();
+    const int64_t waves = nb * blocks_per_node * 4;
+    if (most == 1 || waves <= (sizeof(T) == 8 ? 1536 : 3072)) return 1;
+    if (most == 2) return 2;
+    return waves / 4 >= (CH == 1 ? 2048 : 2 * 3072) ? 4 : CH == 1 ? 2 : 3;
+}
+
 template <typename T, int N, int CH, int NB, int SMAX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void radial_vss_kernel(RadialArgs<T> a) {
+__global__ __launch_bounds__(256, (vss_wpe<T, CH>())) void radial_vss_kernel(RadialArgs<T> a) {
     constexpr int NP = N / CH;
     constexpr int KZH = N / 2 + 1;
     constexpr int64_t N2 = int64_t(N) * N, N3 = N2 * N, PCH = int64_t(NP) * N * KZH;
@@ -1593,23 +1649,33 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
     ra.nslots = ss.nslots;
     ra.K2 = p.K2;
     const int64_t pch = int64_t(N / CH) * N * (N / 2 + 1);
-    // VSS with few slots: the fused kernel (NB nodes x every slot per thread, accumulators
-    // of NB x SMAX x CH complex doubles kept to at most 16 of them)
-    constexpr int NB2 = (2 * CH <= 4) ? 4 : (2 * CH <= 8 ? 2 : 1);
-    constexpr int NB4 = (4 * CH <= 4) ? 4 : (4 * CH <= 8 ? 2 : 1);
     const int64_t rthreads = int64_t(nb) * ss.nslots * pch;
     if constexpr (VSS) {
+        // few slots: every slot of vss_nodes nodes in one thread
+        const int64_t eblocks = (pch + 255) / 256;
+        auto fused = [&](auto smax) {
+            constexpr int SMAX = decltype(smax)::value, MOST = vss_nb_max<T, CH, SMAX>();
+            const int NB = vss_nodes<T, CH, SMAX>(nb, eblocks);
+            const dim3 grid(unsigned(((nb + NB - 1) / NB) * eblocks)), block(256);
+            if (NB == 1) radial_vss_kernel<T, N, CH, 1, SMAX><<<grid, block, 0, st>>>(ra);
+            if constexpr (MOST >= 2)
+                if (NB == 2) radial_vss_kernel<T, N, CH, 2, SMAX><<<grid, block, 0, st>>>(ra);
+            if constexpr (MOST >= 4) {
+                if (NB == 3) radial_vss_kernel<T, N, CH, 3, SMAX><<<grid, block, 0, st>>>(ra);
+                if (NB == 4) radial_vss_kernel<T, N, CH, 4, SMAX><<<grid, block, 0, st>>>(ra);
+            }
+        };
         if (ss.nslots <= 2) {
-            const int64_t blocks = int64_t((nb + NB2 - 1) / NB2) * ((pch + 255) / 256);
-            radial_vss_kernel<T, N, CH, NB2, 2><<<dim3(unsigned(blocks)), dim3(256), 0, st>>>(ra);
+            fused(std::integral_constant<int, 2>{});
         } else if (ss.nslots <= 4) {
-            const int64_t blocks = int64_t((nb + NB4 - 1) / NB4) * ((pch + 255) / 256);
-            radial_vss_kernel<T, N, CH, NB4, 4><<<dim3(unsigned(blocks)), dim3(256), 0, st>>>(ra);
+            fused(std::integral_constant<int, 4>{});
         } else {
-            radial_kernel<T, N, CH, true><<<dim3(unsigned((rthreads + 255) / 256)), dim3(256), 0, st>>>(ra);
+            radial_kernel<T, N, CH, true, 1><<<dim3(unsigned((rthreads + 255) / 256)), dim3(256), 0, st>>>(ra);
         }
     } else {
-        radial_kernel<T, N, CH, false><<<dim3(unsigned((rthreads + 255) / 256)), dim3(256), 0, st>>>(ra);
+        constexpr int QS = radial_qs<N>();
+        constexpr int64_t EL = 256 / QS;
+        radial_kernel<T, N, CH, false, QS><<<dim3(unsigned((rthreads + EL - 1) / EL)), dim3(256), 0, st>>>(ra);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     mark(3);
