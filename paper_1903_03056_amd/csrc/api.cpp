@@ -739,7 +739,7 @@ dgfs_status run_parts(const dgfs_plan& P, const void* f, void* Q, int64_t nb, vo
                                       X + size_t(k) * n3 * E, int64_t(sg) * n3, map(part.t_in[k]), nb, false, tmp, st)))
                 return fail(DGFS_EDEVICE, "kernel launch failed (grid move)");
         }
-        hipError_t e = dgfs::launch_collide(*part.plan, X, Y, nb, w + lay.sub, pairs, st, ev);
+        hipError_t e = dgfs::launch_collide(*part.plan, X, Y, nb, dgfs::Scratch{w + lay.sub, lay.X - lay.sub}, pairs, st, ev);
         if (e != hipSuccess) return fail(DGFS_EDEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         for (int k = 0; k < sg; ++k) {
             const int i = part.species[k];
@@ -818,6 +818,11 @@ size_t dgfs_plan::ws_per_node(bool pairs) const {
     // the matrix-core gain's prepared inputs (one alignment more: ws_slack)
     const size_t prep = geo.CZ == 0 ? size_t(s) * dgfs::mfma_prep_bytes : 0;
     return c * size_t(s) + 2 * half * size_t(nslots) + part * classes.size() * size_t(nrho) + prep;
+}
+
+size_t dgfs_plan::ws_split(int64_t nb) const {
+    if (!parts.empty() || inner || vss || !dgfs::split_directions(N, precision, geo, int(classes.size()), nrho, nb)) return 0;
+    return detail_align(size_t(nb) * total_dirs * nrho * n3() * elem());
 }
 
 extern "C" {
@@ -913,7 +918,8 @@ dgfs_status dgfs_workspace_size(const dgfs_plan* plan, int64_t batch, size_t* by
     if (batch < 1) return fail(DGFS_EINVAL, "batch must be >= 1");
     // the pair-resolved mode needs the larger slot set; size for it (and at least what
     // the plain FP64 path needs for one node)
-    *bytes = std::max(plan->ws_per_node(true) * size_t(batch) + plan->ws_slack(), dgfs::plain_ws_bytes(*plan) + 256);
+    *bytes = std::max(plan->ws_per_node(true) * size_t(batch) + plan->ws_slack() + plan->ws_split(batch),
+                      dgfs::plain_ws_bytes(*plan) + 256);
     return DGFS_OK;
 }
 
@@ -948,8 +954,8 @@ static dgfs_status collide_impl(const dgfs_plan* plan, const void* f, void* Q, i
             continue;
         }
         hipError_t e = dgfs::launch_collide(*plan, static_cast<const char*>(f) + b0 * in_stride,
-                                            static_cast<char*>(Q) + b0 * out_stride, nb, ws, pairs, st,
-                                            stage_ms ? ev : nullptr);
+                                            static_cast<char*>(Q) + b0 * out_stride, nb, dgfs::Scratch{ws, ws_bytes}, pairs,
+                                            st, stage_ms ? ev : nullptr);
         if (e != hipSuccess) {
             result = fail(DGFS_EDEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
             break;
@@ -1040,7 +1046,7 @@ dgfs_status dgfs_relax_workspace_size(const dgfs_plan* plan, int64_t batch, int3
     if (batch < 1) return fail(DGFS_EINVAL, "batch must be >= 1");
     if (scheme != DGFS_EULER && scheme != DGFS_SSPRK2) return fail(DGFS_EINVAL, "unknown scheme");
     *bytes = state_bytes(plan, batch) * (scheme == DGFS_SSPRK2 ? 2 : 1) + plan->ws_per_node(false) * size_t(batch) +
-             plan->ws_slack();
+             plan->ws_slack() + plan->ws_split(batch);
     return DGFS_OK;
 }
 

@@ -204,6 +204,8 @@ hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T
     ga.ncls = ncls;
     ga.nrho = inner.nrho;
     ga.nb = nb;
+    ga.D = nullptr;
+    ga.tdirs = inner.total_dirs;
     gain_kernel<T, NI, CH, CZ, PIPE_OFF, false, GAIN_COMPLEX>
         <<<dim3(gain_groups(nb, int64_t(ncls) * inner.nrho * CH)), dim3(GainK<T, NI, CH, CZ>::NT), 0, st>>>(ga);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -26,7 +26,9 @@ namespace dgfs {
 //               stored), and their imaginary parts, which reach the result only on the
 //               planes k_x, k_y or k_z = N/2 (the literal Nyquist reading), are reduced
 //               to those planes (sums with (-1)^x, (-1)^y, (-1)^z) and stored.
-enum { GAIN_REAL = 0, GAIN_COMPLEX = 1, GAIN_VSS = 2 };
+// GAIN_TERMS    one direction of a GAIN_REAL item: its Re(A B) alone, stored unweighted in
+//               physical space for gain_sum_kernel (split_directions).
+enum { GAIN_REAL = 0, GAIN_COMPLEX = 1, GAIN_VSS = 2, GAIN_TERMS = 3 };
 
 // How the x-pass issues the loads of the next sub-sequence while it combines the current
 // one, chosen per geometry by measurement (tiles_<N>.hip, vss_<N>.hip): not at all, in a
@@ -110,7 +112,8 @@ struct GainArgs {
     const T* nyq;       // [dirs][nrho][2]         2 sin(theta_x N / 2) of the x-phase
     const int* cls;     // [ncls][4] = i, j, ndir, dir_offset
     const T* wdir;      // [ncls]
-    int s, ncls, nrho, nb;
+    T* D;               // GAIN_TERMS: [nb][dirs][nrho][CH][N/CZ][threads]  Re(A B) of one direction
+    int s, ncls, nrho, nb, tdirs;
 };
 
 // out[j] = X[CZ j + CZI] of the length-N DFT (sign SIGN) of the sequence
@@ -853,18 +856,22 @@ __device__ __forceinline__ void store_partial(cx<T>* buf, cx<T>* Pq, int c) {
 template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, int MODE>
 __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArgs<T> a) {
     using K = GainK<T, N, CH, CZ>;
-    constexpr bool CPLX = MODE != GAIN_REAL;  // the whole spectrum of a complex field is stored
+    constexpr bool CPLX = MODE == GAIN_COMPLEX || MODE == GAIN_VSS;  // the whole spectrum of a complex field is stored
     static_assert(!(PACK && CPLX), "the packed two-field form keeps only Re(A B)");
     __shared__ cx<T> buf[K::LDS + ((PACK && pack_ok<T, N, CH, CZ>()) ? K::LINES : 0)];
     int b, item;
-    if (!gain_item<1>(blockIdx.x, a.nb, a.ncls * a.nrho * CH, b, item)) return;
+    // the items of a node: classes, or with GAIN_TERMS the directions of all classes
+    if (!gain_item<1>(blockIdx.x, a.nb, (MODE == GAIN_TERMS ? a.tdirs : a.ncls) * a.nrho * CH, b, item)) return;
     const int c = item % CH;
     item /= CH;
     const int q = item % a.nrho;
-    const int cl = item / a.nrho;
+    int cl = item / a.nrho, dir = 0;
+    if constexpr (MODE == GAIN_TERMS) {
+        for (dir = cl, cl = 0; dir >= a.cls[4 * cl + 2]; ++cl) dir -= a.cls[4 * cl + 2];
+    }
     const int ci = a.cls[4 * cl], cj = a.cls[4 * cl + 1];
     const int ndir = a.cls[4 * cl + 2], doff = a.cls[4 * cl + 3];
-    const T w = a.wdir[cl];
+    const T w = MODE == GAIN_TERMS ? T(1) : a.wdir[cl];
     constexpr int64_t N3 = int64_t(N) * N * N;
     const cx<T>* fhi = a.fhat + (int64_t(b) * a.s + ci) * N3;
     const cx<T>* fhj = a.fhat + (int64_t(b) * a.s + cj) * N3;
@@ -950,6 +957,12 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
             for (int n = 0; n < K::NS; ++n) zero[n] = T(0);
             nyquist_planes(1, zero);
         }
+    } else if constexpr (MODE == GAIN_TERMS) {
+        direction(dir, S);
+        T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + dir) * a.nrho + q) * CH + c) * int64_t(K::NT * K::NS) + tid;
+#pragma unroll
+        for (int j = 0; j < K::NS; ++j) Dq[j * K::NT] = S[j];
+        return;
     } else {
         for (int d = 0; d < ndir; ++d) direction(d, S);
     }
@@ -964,6 +977,40 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
     __syncthreads();
     cx<T>* Pq = a.P + ((int64_t(b) * a.ncls + cl) * a.nrho + q) * int64_t(CH) * K::NP * (CPLX ? K::NPENF : K::NPEN);
     store_partial<T, N, CH, CZ, CPLX>(buf, Pq, c);
+}
+
+// The second half of a split gain: S_q of one item from its directions' terms, summed in the
+// order and with the rounding of gain_kernel (so a node's result does not depend on the
+// split), then the forward transform of the chunk.
+template <typename T, int N, int CH, int CZ>
+__global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_sum_kernel(GainArgs<T> a) {
+    using K = GainK<T, N, CH, CZ>;
+    __shared__ cx<T> buf[K::LDS];
+    int b, item;
+    if (!gain_item<1>(blockIdx.x, a.nb, a.ncls * a.nrho * CH, b, item)) return;
+    const int c = item % CH;
+    item /= CH;
+    const int q = item % a.nrho;
+    const int cl = item / a.nrho;
+    const int ndir = a.cls[4 * cl + 2], doff = a.cls[4 * cl + 3];
+    const T w = a.wdir[cl];
+    const int tid = threadIdx.x;
+    const int cz = tid / K::NTC, u = tid % K::NTC;
+    const int m = u / N, r = u % N;
+    T S[K::NS];
+#pragma unroll
+    for (int j = 0; j < K::NS; ++j) S[j] = T(0);
+#pragma unroll 2
+    for (int d = 0; d < ndir; ++d) {
+        const T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + d) * a.nrho + q) * CH + c) * int64_t(K::NT * K::NS) + tid;
+#pragma unroll
+        for (int j = 0; j < K::NS; ++j) S[j] = fma(w, Dq[j * K::NT], S[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < K::NS; ++j) buf[(m * N + r) * K::ROW + CZ * j + cz] = cx<T>{S[j], T(0)};
+    __syncthreads();
+    cx<T>* Pq = a.P + ((int64_t(b) * a.ncls + cl) * a.nrho + q) * int64_t(CH) * K::NP * K::NPEN;
+    store_partial<T, N, CH, CZ, false>(buf, Pq, c);
 }
 
 // =============================================================== radial kernel
@@ -1566,7 +1613,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // after gain, after radial, after the inverse x/y passes, after the z-pass + combine).
 // MF: the gain stage runs on the matrix cores (FP32, N = 32, VHS only).
 template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, bool VSS, bool MF = false>
-hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                      hipEvent_t* ev) {
     static_assert(!MF || (std::is_same_v<T, float> && N == 32 && CH == 2 && !VSS), "matrix-core gain: FP32 VHS N = 32");
     constexpr int MODE = VSS ? GAIN_VSS : GAIN_REAL;
@@ -1576,7 +1623,7 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
     const SlotSet& ss = pairs ? p.pair_slots : p.sum_slots;
     constexpr int64_t N3 = int64_t(N) * N * N;
     const int ncls = int(p.classes.size());
-    char* w = static_cast<char*>(ws);
+    char* w = static_cast<char*>(ws.p);
     cx<T>* fhat = reinterpret_cast<cx<T>*>(w);
     w += align256(sizeof(cx<T>) * nb * p.s * N3);
     cx<T>* P = reinterpret_cast<cx<T>*>(w);
@@ -1612,6 +1659,8 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
     ga.ncls = ncls;
     ga.nrho = p.nrho;
     ga.nb = nb;
+    ga.D = nullptr;
+    ga.tdirs = p.total_dirs;
     if constexpr (MF) {
         // the prepared inputs follow the loss spectra
         char* prep = reinterpret_cast<char*>(Lt + int64_t(nb) * ss.nslots * NH);
@@ -1619,7 +1668,22 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
         if ((e = launch_gain_mfma32(p, f, P, prep, nb, st)) != hipSuccess) return e;
     } else {
         const int64_t ipn = int64_t(ncls) * p.nrho * CH;
-        gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<dim3(gain_groups(nb, ipn)), dim3(GainK<T, N, CH, CZ>::NT), 0, st>>>(ga);
+        const dim3 grid(gain_groups(nb, ipn)), block(GainK<T, N, CH, CZ>::NT);
+        bool split = false;
+        if constexpr (!VSS && N <= 32) {
+            // the terms follow the loss spectra, where the caller's workspace reaches so far
+            char* terms = reinterpret_cast<char*>(Lt + int64_t(nb) * ss.nslots * NH);
+            terms += (256 - reinterpret_cast<uintptr_t>(terms) % 256) % 256;
+            const size_t bytes = p.ws_split(nb), used = size_t(terms - static_cast<char*>(ws.p));
+            if (bytes != 0 && used <= ws.bytes && bytes <= ws.bytes - used) {
+                split = true;
+                ga.D = reinterpret_cast<T*>(terms);
+                gain_kernel<T, N, CH, CZ, PIPE, PACK, GAIN_TERMS>
+                    <<<dim3(gain_groups(nb, int64_t(p.total_dirs) * p.nrho * CH)), block, 0, st>>>(ga);
+                gain_sum_kernel<T, N, CH, CZ><<<grid, block, 0, st>>>(ga);
+            }
+        }
+        if (!split) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<grid, block, 0, st>>>(ga);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if constexpr (VSS) {
@@ -1699,24 +1763,24 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, void* ws, boo
 }  // namespace detail
 
 // Per-N entry points (tiles_<N>.hip): run one slice with the plan's tile geometry.
-hipError_t run_tiles_16(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_tiles_16(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                         hipEvent_t* ev);
-hipError_t run_tiles_24(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_tiles_24(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                         hipEvent_t* ev);
-hipError_t run_tiles_32(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_tiles_32(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                         hipEvent_t* ev);
-hipError_t run_tiles_48(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_tiles_48(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                         hipEvent_t* ev);
-hipError_t run_tiles_64(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_tiles_64(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                         hipEvent_t* ev);
 // The same for plans with a VSS kernel (vss_<N>.hip).
-hipError_t run_vss_16(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_vss_16(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                       hipEvent_t* ev);
-hipError_t run_vss_24(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_vss_24(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                       hipEvent_t* ev);
-hipError_t run_vss_32(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_vss_32(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                       hipEvent_t* ev);
-hipError_t run_vss_48(const dgfs_plan& p, const void* f, void* Q, int nb, void* ws, bool pairs, hipStream_t st,
+hipError_t run_vss_48(const dgfs_plan& p, const void* f, void* Q, int nb, Scratch ws, bool pairs, hipStream_t st,
                       hipEvent_t* ev);
 
 }  // namespace dgfs

@@ -237,14 +237,14 @@ bool gain_geometry(int N, int precision, GainGeometry* g, bool matrix_ok) {
     return false;
 }
 
-hipError_t launch_collide(const dgfs_plan& p, const void* f, void* Q, int64_t nb, void* ws, bool pairs,
+hipError_t launch_collide(const dgfs_plan& p, const void* f, void* Q, int64_t nb, Scratch ws, bool pairs,
                           hipStream_t st, hipEvent_t* ev) {
     if (p.inner) {
         switch (p.N) {
-            case 16: return run_dealias_16(p, *p.inner, f, Q, int(nb), ws, pairs, st, ev);
-            case 24: return run_dealias_24(p, *p.inner, f, Q, int(nb), ws, pairs, st, ev);
-            case 32: return run_dealias_32(p, *p.inner, f, Q, int(nb), ws, pairs, st, ev);
-            case 48: return run_dealias_48(p, *p.inner, f, Q, int(nb), ws, pairs, st, ev);
+            case 16: return run_dealias_16(p, *p.inner, f, Q, int(nb), ws.p, pairs, st, ev);
+            case 24: return run_dealias_24(p, *p.inner, f, Q, int(nb), ws.p, pairs, st, ev);
+            case 32: return run_dealias_32(p, *p.inner, f, Q, int(nb), ws.p, pairs, st, ev);
+            case 48: return run_dealias_48(p, *p.inner, f, Q, int(nb), ws.p, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
     }

@@ -25,6 +25,20 @@ struct GainGeometry {
 // The default: the first compiled geometry, skipping the matrix-core ones (CZ = 0: FP32
 // VHS plans of the circular form) unless matrix_ok.
 bool gain_geometry(int N, int precision, GainGeometry* g, bool matrix_ok = true);
+// Whether a call of nb nodes spreads the directions of its gain items over the chip, one
+// workgroup per (item, direction), and sums them in a second kernel (gain.hpp).  An item runs
+// up to M directions one after the other, so a call whose items do not fill the CUs takes M
+// directions' time whatever its size; the split costs a pass over the terms (one value per
+// point and direction) in memory.  Calls in us, together / split, by items:
+//   FP32 N = 24 (four workgroups to a CU): 324 148 / 89, 432 159 / 115, 648 172 / 134, 972 186 / 180;
+//   FP32 N = 16 (four): 360 101 / 71, 576 104 / 90, 960 129 / 126;
+//   FP64 N = 16 (two): 24 71 / 42, 360 150 / 116, 576 149 / 160;  FP64 N = 24 (two): 324 200 / 239;
+//   FP64 N = 32 (one): 384 341 / 302, 576 442 / 456.
+// Above N = 32 a node has more items than the chip has CUs.
+inline bool split_directions(int N, int precision, const GainGeometry& geo, int ncls, int nrho, int64_t nb) {
+    const int64_t most = precision == 0 && N <= 24 ? 960 : N == 24 ? 256 : 400;   // precision 0: FP32
+    return N <= 32 && geo.CZ > 0 && nb * ncls * nrho * geo.CH <= most;
+}
 // Bytes per (node, species) of the matrix-core gain's prepared input (N = 32): f split into
 // FP16 hi and lo, the alternating x-sum plane split likewise, and 64 FP32 scalars.
 constexpr size_t mfma_prep_bytes = (2 * 32768 + 2048) * 2 + 64 * 4;
@@ -113,12 +127,21 @@ struct dgfs_plan {
     // workspace bytes per node, and the alignment slack added once per call
     size_t ws_per_node(bool pairs) const;
     size_t ws_slack() const { return parts.empty() ? 4 * 256 : 12 * 256; }
+    // bytes beyond those with which a call of nb nodes spreads its gain directions over the
+    // chip (gain.hpp); 0 where it does not
+    size_t ws_split(int64_t nb) const;
 };
 
 namespace dgfs {
+// Device memory of a call: at least ws_per_node() per node (and the alignment slack), and
+// what the caller gave beyond that.
+struct Scratch {
+    void* p;
+    size_t bytes;
+};
 // Launch the full collide pipeline for nb nodes on `stream`.
 // ev: NULL, or 6 events recorded at the stage boundaries of the slice.
-hipError_t launch_collide(const dgfs_plan& p, const void* f, void* Q, int64_t nb, void* ws,
+hipError_t launch_collide(const dgfs_plan& p, const void* f, void* Q, int64_t nb, Scratch ws,
                           bool pairs, hipStream_t stream, hipEvent_t* ev);
 // The dealiased pipeline (vss_24.hip: N = 16, dealias_36.hip: N = 24, vss_48.hip: N = 32,
 // dealias_72.hip: N = 48).

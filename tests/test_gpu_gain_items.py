@@ -1,6 +1,7 @@
 """How the gain's work items are dealt to the chip: whole nodes per XCD for every eight
-nodes, the items of the last nb % 8 nodes over all XCDs.  At the edges of that rule every
-node's result is its result alone, bit for bit, and the oracle's.
+nodes, the items of the last nb % 8 nodes over all XCDs; in small calls one workgroup per direction (N = 16 here up to 44
+nodes, N = 24 up to 35).  At the edges of those rules every node's result is its result alone,
+bit for bit, and the oracle's; so it is where the workspace has no room for the split.
 
 Tolerances: relative L-inf over each (node, species) against the FP64 oracle, 1e-12 for
 FP64 and 1e-5 for FP32 plans, as in the other parity tests."""
@@ -16,7 +17,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("N,precision", [(16, "f64"), (24, "f32"), (32, "f32")])
-@pytest.mark.parametrize("batch", [1, 7, 8, 9, 39])
+@pytest.mark.parametrize("batch", [1, 7, 8, 9, 39, 45])
 def test_every_node_at_the_edges_of_the_dealing(N, precision, batch):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -29,6 +30,12 @@ def test_every_node_at_the_edges_of_the_dealing(N, precision, batch):
     Q = plan.collide(ft)
     for b in range(batch):
         assert torch.equal(plan.collide(ft[b:b + 1].contiguous())[0], Q[b]), b
+    if batch == 7:
+        # per node and alignment only, without what the split asks for beyond that
+        per = (plan.workspace_bytes(2000) - plan.workspace_bytes(1000)) // 1000
+        tight = torch.empty(per * batch + 1024, dtype=torch.uint8, device="cuda")
+        assert tight.numel() <= plan.workspace_bytes(batch)
+        assert torch.equal(plan.collide(ft, workspace=tight), Q)
     ref = OS.collide(ft[batch - 1].double().cpu().numpy(), OS.vhs_problem(masses, 0.74, L, N, M, nrho))
     got = Q[batch - 1].double().cpu().numpy()
     err = float(np.max(np.abs(got - ref).reshape(2, -1).max(1) / np.abs(ref).reshape(2, -1).max(1)))
