@@ -402,6 +402,10 @@ void build_tables(dgfs_plan& P, std::vector<char>& blob) {
     push_real<T>(blob, P.off_nyq, nyq);
     push_int(blob, P.off_cls, cls);
     push_real<T>(blob, P.off_wdir, wdir);
+    std::vector<int> ord(P.classes.size());  // classes, most directions first
+    for (size_t k = 0; k < ord.size(); ++k) ord[k] = int(k);
+    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return P.classes[x].ndir > P.classes[y].ndir; });
+    push_int(blob, P.off_ord, ord);
 
     // ---------------- F tables per (class, target) and G tables per ordered pair
     const int K2 = P.K2;

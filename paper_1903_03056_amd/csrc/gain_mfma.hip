@@ -58,6 +58,7 @@ struct Args {
     const float* sc;       // [dirs][nrho][2 fields][4]: s_x, s_y, s_z
     const int* cls;        // [ncls][4] = i, j, ndir, dir_offset
     const float* wdir;     // [ncls]
+    const int* ord;        // [ncls] classes, most directions first
     cx<float>* P;          // chunk partials, as gain_kernel<float, 32, 2, 1>
     int s, ncls, nrho, nb;
 };
@@ -557,7 +558,7 @@ __global__ __launch_bounds__(NT) void gain_kernel(Args a) {
     __shared__ Smem sm;
     Lds& L = sm.m;
     int b, item;
-    if (!gain_item<NG>(blockIdx.x, a.nb, a.ncls * a.nrho * 2, b, item)) return;
+    if (!gain_item<NG>(blockIdx.x, a.nb, a.ncls, a.nrho * 2, a.ord, b, item)) return;
     const int c = item % 2;
     item /= 2;
     const int q = item % a.nrho;
@@ -629,6 +630,7 @@ hipError_t launch_gain_mfma32(const dgfs_plan& p, const float* f, cx<float>* P, 
     a.sc = reinterpret_cast<const float*>(dev + p.off_msc);
     a.cls = reinterpret_cast<const int*>(dev + p.off_cls);
     a.wdir = reinterpret_cast<const float*>(dev + p.off_wdir);
+    a.ord = reinterpret_cast<const int*>(dev + p.off_ord);
     a.P = P;
     a.s = p.s;
     a.ncls = int(p.classes.size());
