@@ -406,6 +406,11 @@ void build_tables(dgfs_plan& P, std::vector<char>& blob) {
     for (size_t k = 0; k < ord.size(); ++k) ord[k] = int(k);
     std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return P.classes[x].ndir > P.classes[y].ndir; });
     push_int(blob, P.off_ord, ord);
+    std::vector<int> xs(size_t(P.total_dirs), 0);  // same sigma_x as the direction before it in its class
+    for (const auto& c : P.classes)
+        for (int d = 1; d < c.ndir; ++d)
+            xs[size_t(c.dir_offset + d)] = P.sigma[3 * c.dirs[d]] == P.sigma[3 * c.dirs[d - 1]] ? 1 : 0;
+    push_int(blob, P.off_xs, xs);
 
     // ---------------- F tables per (class, target) and G tables per ordered pair
     const int K2 = P.K2;

@@ -205,6 +205,7 @@ hipError_t run_dealiased(const dgfs_plan& outer, const dgfs_plan& inner, const T
     ga.nrho = inner.nrho;
     ga.nb = nb;
     ga.ord = reinterpret_cast<const int*>(dev + inner.off_ord);
+    ga.xs = reinterpret_cast<const int*>(dev + inner.off_xs);
     ga.D = nullptr;
     ga.tdirs = inner.total_dirs;
     gain_kernel<T, NI, CH, CZ, PIPE_OFF, false, GAIN_COMPLEX>

@@ -118,6 +118,7 @@ struct GainArgs {
     const int* cls;     // [ncls][4] = i, j, ndir, dir_offset
     const T* wdir;      // [ncls]
     const int* ord;     // [ncls] classes, most directions first
+    const int* xs;      // [dirs]  1: the direction before it in its class has the same sigma_x
     T* D;               // GAIN_TERMS: [nb][dirs][nrho][CH][N/CZ][threads]  Re(A B) of one direction
     int s, ncls, nrho, nb, tdirs;
 };
@@ -288,6 +289,30 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
     }
 }
 
+// The x-transformed pencils of a direction, kept by their threads for the next direction of
+// its class.  The x-pass depends on a direction through its sigma_x alone, and the design's
+// points are sorted by it, so a class's directions come in runs of one sigma_x: of 12
+// directions (icosahedron) 5 are fresh, of 6 (half of them) 3, of 24 6, of the octahedron's 6
+// 3.  The others take the kept values back (the same values: nothing is rounded again)
+// instead of reading the spectrum and combining it anew.  It pays where the values find room in
+// registers or where the x-pass is most of the kernel.  VSS calls, us without / with: 96
+// argon-krypton nodes at N = 32 8657 / 7888, FP64 at N = 32 (8 nodes) 2043 / 1891, at N = 24
+// (20) 1588 / 1413, at N = 16 (60) 780 / 758, FP32 at N = 24 (40) 1243 / 1235; but FP32 at N =
+// 16 (100) 486 / 492 and N = 48 (5) 2401 / 2476.  VHS calls at N = 64: FP32 (2) 4554 / 4027,
+// FP64 (1) 6016 / 5823; but dealiased N = 32 (10) 1998 / 2460, FP32 at N = 24 (63 nodes, DG)
+// 3208 / 3641, N = 16 (300) 583 / 722 (a wavefront per SIMD less) and the packed N = 48 form (7)
+// 2296 / 3022 (two fields' values in private memory; in a place of the workspace per
+// workgroup, 8 nodes of three species, 5.7 / 7.1 ms in the gain).
+template <typename T, int N, int MODE>
+constexpr bool keep_ok() {
+    return MODE == GAIN_VSS ? N < 48 && (N > 16 || sizeof(T) == 8) : MODE == GAIN_REAL && N == 64;
+}
+template <int NP, typename T>
+__device__ __forceinline__ void keep_x(cx<T>* to, const cx<T>* from) {
+#pragma unroll
+    for (int l = 0; l < NP; ++l) to[l] = from[l];
+}
+
 // Chunk c of IDFT(f_hat * phase) for one shifted field: out[j] at (x = CH m + c,
 // y = r, z = CZ j + cz).  The x-pass reads the spectrum from global memory (coalesced
 // over (l_y, l_z)) and keeps only the chunk's x-outputs: the CH strided input
@@ -314,10 +339,11 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
 // x-pencils are transformed, from 2/3 of their inputs, and stored with their own y/z phase;
 // the y- and z-passes skip the zero rows and columns.  (Ten FP32 nodes padded to 48^3, whole call: every
 // pencil transformed 4.04 ms, the kept ones 2.14 ms; two load buffers in turn: no change.)
-template <typename T, int N, int CH, int CZ, int PIPE, bool HERM = true>
+template <typename T, int N, int CH, int CZ, int PIPE, bool HERM, bool KEEP>
 __device__ __forceinline__ void field_ifft(const cx<T>* __restrict__ fh, const cx<T>* __restrict__ kxt,
                                            const cx<T>* __restrict__ yzt, T nyq, int c, cx<T>* buf, int cz,
-                                           int m, int r, cx<T>* out) {
+                                           int m, int r, cx<T>* out, bool fresh,
+                                           cx<T> (*kept)[GainK<T, N, CH, CZ>::NP]) {
     using K = GainK<T, N, CH, CZ>;
     if constexpr (!HERM) {
         constexpr int ES = int(sizeof(cx<T>));
@@ -369,55 +395,60 @@ __device__ __forceinline__ void field_ifft(const cx<T>* __restrict__ fh, const c
         const int P = ly * N + lz;
         const int vo = P * ES;
         cx<T> y[K::NP];
+        if (!KEEP || fresh) {
 #pragma unroll
-        for (int l = 0; l < K::NP; ++l) y[l] = cx<T>{T(0), T(0)};
-        if (SELF && __ballot(!paired) != 0) {
-            // f(., P1) + i mk f(., P2) with both loads of an index issued together
-            const int vo2 = paired ? vo : vo + (N / 2) * ES;
-            const T mk = paired ? T(0) : T(1);
+            for (int l = 0; l < K::NP; ++l) y[l] = cx<T>{T(0), T(0)};
+            if (SELF && __ballot(!paired) != 0) {
+                // f(., P1) + i mk f(., P2) with both loads of an index issued together
+                const int vo2 = paired ? vo : vo + (N / 2) * ES;
+                const T mk = paired ? T(0) : T(1);
 #pragma unroll 1
-            for (int t = 0; t < CH; ++t) {
-                cx<T> a[K::NP], b[K::NP];
+                for (int t = 0; t < CH; ++t) {
+                    cx<T> a[K::NP], b[K::NP];
 #pragma unroll
-                for (int l = 0; l < K::NP; ++l) {
-                    a[l] = bload<T>(rs, vo, (l + t * K::NP) * RS);
-                    b[l] = bload<T>(rs, vo2, (l + t * K::NP) * RS);
+                    for (int l = 0; l < K::NP; ++l) {
+                        a[l] = bload<T>(rs, vo, (l + t * K::NP) * RS);
+                        b[l] = bload<T>(rs, vo2, (l + t * K::NP) * RS);
+                    }
+#pragma unroll
+                    for (int l = 0; l < K::NP; ++l)
+                        cmac(y[l], cx<T>{a[l].x - mk * b[l].y, a[l].y + mk * b[l].x}, kxt[l + t * K::NP]);
                 }
+            } else if constexpr (PIPE == PIPE_TWO) {
+                const cx<T>* const kx1[1] = {kxt};
+                cx<T>* const y1[1] = {y};
+                x_sum_pipe<T, K::NP, CH, 1>(rs, vo, RS, kx1, y1);
+            } else if constexpr (PIPE == PIPE_ROTATE) {
+                cx<T> nxt[K::NP];
 #pragma unroll
-                for (int l = 0; l < K::NP; ++l)
-                    cmac(y[l], cx<T>{a[l].x - mk * b[l].y, a[l].y + mk * b[l].x}, kxt[l + t * K::NP]);
-            }
-        } else if constexpr (PIPE == PIPE_TWO) {
-            const cx<T>* const kx1[1] = {kxt};
-            cx<T>* const y1[1] = {y};
-            x_sum_pipe<T, K::NP, CH, 1>(rs, vo, RS, kx1, y1);
-        } else if constexpr (PIPE == PIPE_ROTATE) {
-            cx<T> nxt[K::NP];
-#pragma unroll
-            for (int l = 0; l < K::NP; ++l) nxt[l] = bload<T>(rs, vo, l * RS);
+                for (int l = 0; l < K::NP; ++l) nxt[l] = bload<T>(rs, vo, l * RS);
 #pragma unroll 1
-            for (int t = 0; t < CH; ++t) {
-                cx<T> cur[K::NP];
+                for (int t = 0; t < CH; ++t) {
+                    cx<T> cur[K::NP];
 #pragma unroll
-                for (int l = 0; l < K::NP; ++l) cur[l] = nxt[l];
-                if (t + 1 < CH) {
+                    for (int l = 0; l < K::NP; ++l) cur[l] = nxt[l];
+                    if (t + 1 < CH) {
 #pragma unroll
-                    for (int l = 0; l < K::NP; ++l) nxt[l] = bload<T>(rs, vo, (l + (t + 1) * K::NP) * RS);
+                        for (int l = 0; l < K::NP; ++l) nxt[l] = bload<T>(rs, vo, (l + (t + 1) * K::NP) * RS);
+                    }
+#pragma unroll
+                    for (int l = 0; l < K::NP; ++l) cmac(y[l], cur[l], kxt[l + t * K::NP]);
                 }
+            } else {
+#pragma unroll 1
+                for (int t = 0; t < CH; ++t) {
 #pragma unroll
-                for (int l = 0; l < K::NP; ++l) cmac(y[l], cur[l], kxt[l + t * K::NP]);
+                    for (int l = 0; l < K::NP; ++l) {
+                        const int jx = l + t * K::NP;
+                        cmac(y[l], bload<T>(rs, vo, jx * RS), kxt[jx]);
+                    }
+                }
             }
+            fft<K::NP, +1>(y);
+            if constexpr (KEEP) keep_x<K::NP>(kept[k], y);
         } else {
-#pragma unroll 1
-            for (int t = 0; t < CH; ++t) {
-#pragma unroll
-                for (int l = 0; l < K::NP; ++l) {
-                    const int jx = l + t * K::NP;
-                    cmac(y[l], bload<T>(rs, vo, jx * RS), kxt[jx]);
-                }
-            }
+            if constexpr (KEEP) keep_x<K::NP>(y, kept[k]);
         }
-        fft<K::NP, +1>(y);
         const cx<T> fn = bload<T>(rs, vo, (N / 2) * RS);
         if (SELF && !paired) {
             const T h1 = T(0.5) * nyq * fn.x;
@@ -956,7 +987,12 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
         __syncthreads();
     };
 
+    // what at most this many rounds of the x-pass leave (keep_x)
+    constexpr bool KEEP = keep_ok<T, N, MODE>();
+    constexpr int XR = KEEP ? (N * N / 2 + 2 + K::NT - 1) / K::NT : 1;
+    cx<T> kept[2][XR][K::NP];
     auto direction = [&](int d, T* Sd) {
+        const bool fresh = !KEEP || d == 0 || a.xs[doff + d] == 0;
         const int64_t base = (int64_t(doff + d) * a.nrho + q) * 2;
         if constexpr (PACK && pack_ok<T, N, CH, CZ>()) {
             packed_direction<T, N, CH, CZ, PIPE>(fhi, fhj, a.kx + ((base + 0) * CH + c) * N, a.yz + (base + 0) * 2 * N,
@@ -965,10 +1001,10 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
         } else {
             cx<T> A[K::NS], B[K::NS];
             constexpr bool HERM = MODE != GAIN_COMPLEX;
-            field_ifft<T, N, CH, CZ, PIPE, HERM>(fhi, a.kx + ((base + 0) * CH + c) * N, a.yz + (base + 0) * 2 * N,
-                                                 a.nyq[base], c, buf, cz, m, r, A);
-            field_ifft<T, N, CH, CZ, PIPE, HERM>(fhj, a.kx + ((base + 1) * CH + c) * N, a.yz + (base + 1) * 2 * N,
-                                                 a.nyq[base + 1], c, buf, cz, m, r, B);
+            field_ifft<T, N, CH, CZ, PIPE, HERM, KEEP>(fhi, a.kx + ((base + 0) * CH + c) * N, a.yz + (base + 0) * 2 * N,
+                                                       a.nyq[base], c, buf, cz, m, r, A, fresh, kept[0]);
+            field_ifft<T, N, CH, CZ, PIPE, HERM, KEEP>(fhj, a.kx + ((base + 1) * CH + c) * N, a.yz + (base + 1) * 2 * N,
+                                                       a.nyq[base + 1], c, buf, cz, m, r, B, fresh, kept[1]);
 #pragma unroll
             for (int n = 0; n < K::NS; ++n) Sd[n] = fma(w, fma(A[n].x, B[n].x, -A[n].y * B[n].y), Sd[n]);
             if constexpr (MODE == GAIN_COMPLEX) {
@@ -1696,6 +1732,7 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, Scratch ws, b
     ga.nrho = p.nrho;
     ga.nb = nb;
     ga.ord = reinterpret_cast<const int*>(dev + p.off_ord);
+    ga.xs = reinterpret_cast<const int*>(dev + p.off_xs);
     ga.D = nullptr;
     ga.tdirs = p.total_dirs;
     if constexpr (MF) {

@@ -99,7 +99,7 @@ struct dgfs_plan {
     void* dev = nullptr;  // one block holding every table
     size_t dev_bytes = 0;
     // byte offsets of the tables in `dev`
-    size_t off_kx = 0, off_yz = 0, off_nyq = 0, off_F = 0, off_G = 0, off_tw = 0, off_cls = 0, off_wdir = 0, off_ord = 0;
+    size_t off_kx = 0, off_yz = 0, off_nyq = 0, off_F = 0, off_G = 0, off_tw = 0, off_cls = 0, off_wdir = 0, off_ord = 0, off_xs = 0;
     // matrix-core gain (geometry CZ = 0): split-FP16 shift-matrix operands and Nyquist
     // coefficients per (direction, rho, field)
     size_t off_mtab = 0, off_msc = 0;
