@@ -708,25 +708,24 @@ dgfs_status create_species_grids(const dgfs_problem* problem, dgfs_plan** out) {
 
 // Byte layout of one part's share of the workspace for nb nodes.
 struct PartLayout {
-    size_t sub, X, Y, tmp, total;
+    size_t X, Y, tmp, sub;
 };
 
 PartLayout part_layout(const dgfs_plan& P, const dgfs_plan::GridPart& part, int64_t nb, bool pairs) {
     const size_t E = P.elem() * P.n3() * size_t(nb);
     const size_t sg = part.species.size();
     PartLayout l;
-    l.sub = 0;
-    l.X = detail_align(part.plan->ws_per_node(pairs) * size_t(nb) + part.plan->ws_slack());
-    l.Y = l.X + detail_align(E * sg);
+    l.X = 0;
+    l.Y = detail_align(E * sg);
     l.tmp = l.Y + detail_align(E * (pairs ? sg * sg : sg));
-    l.total = l.tmp + detail_align(2 * E);
+    l.sub = l.tmp + detail_align(2 * E);   // last: the part's plan takes what is left
     return l;
 }
 
 // One slice of nb nodes through every part.  stage_ms (optional, synchronous): adds the
 // part's stage times, with the moves between grids counted in the first and last stage.
-dgfs_status run_parts(const dgfs_plan& P, const void* f, void* Q, int64_t nb, void* ws, bool pairs, hipStream_t st,
-                      hipEvent_t* ev, float* stage_ms) {
+dgfs_status run_parts(const dgfs_plan& P, const void* f, void* Q, int64_t nb, dgfs::Scratch ws, bool pairs,
+                      hipStream_t st, hipEvent_t* ev, float* stage_ms) {
     const size_t E = P.elem();
     const int64_t n3 = int64_t(P.n3());
     const int s = P.s;
@@ -735,7 +734,7 @@ dgfs_status run_parts(const dgfs_plan& P, const void* f, void* Q, int64_t nb, vo
     for (const auto& part : P.parts) {
         const int sg = int(part.species.size());
         const PartLayout lay = part_layout(P, part, nb, pairs);
-        char* w = static_cast<char*>(ws);
+        char* w = static_cast<char*>(ws.p);
         char* X = w + lay.X;
         char* Y = w + lay.Y;
         char* tmp = w + lay.tmp;
@@ -748,7 +747,7 @@ dgfs_status run_parts(const dgfs_plan& P, const void* f, void* Q, int64_t nb, vo
                                       X + size_t(k) * n3 * E, int64_t(sg) * n3, map(part.t_in[k]), nb, false, tmp, st)))
                 return fail(DGFS_EDEVICE, "kernel launch failed (grid move)");
         }
-        hipError_t e = dgfs::launch_collide(*part.plan, X, Y, nb, dgfs::Scratch{w + lay.sub, lay.X - lay.sub}, pairs, st, ev);
+        hipError_t e = dgfs::launch_collide(*part.plan, X, Y, nb, dgfs::Scratch{w + lay.sub, ws.bytes - lay.sub}, pairs, st, ev);
         if (e != hipSuccess) return fail(DGFS_EDEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         for (int k = 0; k < sg; ++k) {
             const int i = part.species[k];
@@ -830,7 +829,9 @@ size_t dgfs_plan::ws_per_node(bool pairs) const {
 }
 
 size_t dgfs_plan::ws_split(int64_t nb) const {
-    if (!parts.empty() || inner || vss || !dgfs::split_directions(N, precision, geo, int(classes.size()), nrho, nb)) return 0;
+    size_t most = 0;   // the parts run one after the other in the same memory
+    for (const auto& part : parts) most = std::max(most, part.plan->ws_split(nb));
+    if (!parts.empty() || inner || vss || !dgfs::split_directions(N, precision, geo, int(classes.size()), nrho, nb)) return most;
     return detail_align(size_t(nb) * total_dirs * nrho * n3() * elem());
 }
 
@@ -957,8 +958,8 @@ static dgfs_status collide_impl(const dgfs_plan* plan, const void* f, void* Q, i
         const int64_t nb = std::min(slice, batch - b0);
         if (!plan->parts.empty()) {
             result = run_parts(*plan, static_cast<const char*>(f) + b0 * in_stride,
-                               static_cast<char*>(Q) + b0 * out_stride, nb, ws, pairs, st, stage_ms ? ev : nullptr,
-                               stage_ms);
+                               static_cast<char*>(Q) + b0 * out_stride, nb, dgfs::Scratch{ws, ws_bytes}, pairs, st,
+                               stage_ms ? ev : nullptr, stage_ms);
             if (result != DGFS_OK) break;
             continue;
         }
