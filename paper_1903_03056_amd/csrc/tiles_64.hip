@@ -12,7 +12,7 @@ hipError_t run_tiles_64(const dgfs_plan& p, const void* f, void* Q, int nb, Scra
     const int key = p.geo.CH * 100 + p.geo.CZ;
     if (p.precision == DGFS_FP64) {
         switch (key) {
-            case 3208: return detail::run_slice<double, 64, 32, 8, PIPE_TWO, false, false>(
+            case 3208: return detail::run_slice<double, 64, 32, 8, PIPE_ROTATE, false, false>(
                 p, static_cast<const double*>(f), static_cast<double*>(Q), nb, ws, pairs, st, ev);
             default: return hipErrorInvalidValue;
         }
