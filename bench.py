@@ -78,14 +78,20 @@ def gain_flops_per_node_vss(N, M, n_rho, s, antipodal=True):
 
 def mfma_flops_per_launch(batch, N, M, n_rho, s):
     """Matrix-core flops the (2, 0) gain geometry executes per launch: per work item (node,
-    class, rho_q, x-chunk) and field, the x-contraction (8 wavefronts x 8 tiles x 3 split
-    products of 16x16x32), the per-wavefront C_y product of the plane vectors (6 of
-    32x32x16), the two planes' z- and y-contractions (8 x 2 x 12) and the a_x plane (12);
-    two fields per direction, two chunks."""
+    class, rho_q, x-chunk) and field, the per-wavefront C_y product of the plane vectors (6 of
+    32x32x16), the two planes' z- and y-contractions (8 x 2 x 12) and the a_x plane (12), and
+    for the first direction of each run of one sigma_x the x-contraction (8 wavefronts x 8 tiles
+    x 3 split products of 16x16x32); two fields per direction, two chunks."""
+    from paper_1903_03056_amd import design
     assert N == 32
-    per_field = 8 * 8 * 3 * 16384 + 8 * 6 * 32768 + 8 * 2 * 12 * 32768 + 12 * 32768
-    class_dirs = s * (M // 2) + s * (s - 1) // 2 * M   # antipodal design
-    return batch * class_dirs * n_rho * 2 * 2 * per_field
+    x_stage = 8 * 8 * 3 * 16384
+    rest = 8 * 6 * 32768 + 8 * 2 * 12 * 32768 + 12 * 32768
+    pts = design(M)                                    # sorted by sigma_x; antipodal for M = 6, 12
+    half = [i for i, p in enumerate(pts) if i <= int(np.argmin(np.abs(pts + p).sum(axis=1)))]
+    like, unlike = s, s * (s - 1) // 2
+    class_dirs = like * len(half) + unlike * M
+    fresh = like * len(set(pts[half, 0])) + unlike * len(set(pts[:, 0]))
+    return batch * n_rho * 2 * 2 * (class_dirs * rest + fresh * x_stage)
 
 
 def load_traffic():

@@ -143,7 +143,9 @@ dgfs_status dgfs_workspace_size(const dgfs_plan* plan, int64_t batch, size_t* by
 
 /* Q[b][i] = sum_j Q^{ij}(f[b][i], f[b][j]) for b < batch.
  * f, Q: device arrays [batch][s][N^3] of the plan precision; f and Q must not overlap.
- * workspace: device memory, 256-byte aligned, ws_bytes >= dgfs_workspace_size(plan, 1). */
+ * workspace: device memory, 256-byte aligned, ws_bytes >= dgfs_workspace_size(plan, 1).
+ * (That size may count memory with which the gain of a few nodes runs on more of the chip;
+ * a workspace without room for it is accepted too and gives the same result.) */
 dgfs_status dgfs_collide(const dgfs_plan* plan, const void* f, void* Q, int64_t batch,
                          void* workspace, size_t ws_bytes, void* stream);
 
@@ -151,7 +153,7 @@ dgfs_status dgfs_collide(const dgfs_plan* plan, const void* f, void* Q, int64_t 
  * around each stage, the call waits for the work to finish, and stage_ms[0..4]
  * receives the summed durations (over batch slices) of: the forward transform of f,
  * the gain kernel (the sigma/rho loop of Sec. 4), the radial-sum and loss-spectrum
- * kernel, the x- and y-passes of the inverse transforms, and their z-pass fused with
+ * kernel, the x-pass of the inverse transforms, and their y- and z-passes fused with
  * the final combination.  Synchronous. */
 dgfs_status dgfs_collide_timed(const dgfs_plan* plan, const void* f, void* Q, int64_t batch,
                                void* workspace, size_t ws_bytes, void* stream, float* stage_ms);

@@ -249,7 +249,7 @@ class CollisionPlan:
 
     def collide_timed(self, f, out=None, workspace=None, stream=None):
         """dgfs_collide with per-stage HIP-event timing (synchronous).  Returns
-        (Q, stage_ms) with stage_ms = [forward FFT, gain, radial+loss, inverse FFTs, combine]."""
+        (Q, stage_ms) with stage_ms = [forward FFT, gain, radial+loss, inverse x-pass, inverse y, z + combine]."""
         import torch
         self._check_f(f)
         batch = f.shape[0]

@@ -36,8 +36,8 @@ enum { GAIN_REAL = 0, GAIN_COMPLEX = 1, GAIN_VSS = 2, GAIN_TERMS = 3 };
 // alive).  The packed form takes any value but PIPE_OFF as two buffers.  FP64 gains, ms
 // off / rotating / two: N = 16 (200 nodes) 0.527 / 0.442 / 0.427, N = 24 (60) 2.03 / 2.28 /
 // 2.14, N = 32 (32) 3.91 / 3.15 / 3.33, N = 48 (4) 3.62 / 3.02 / 2.93, N = 64 (1) 6.49 / 5.65
-// / 5.59 (4.77 / 5.32 since it keeps x-transforms, below): the 16-byte loads leave few in flight otherwise; at N = 24 the registers cost a
-// wavefront.
+// / 5.59 (4.77 / 5.32 since it keeps x-transforms, below): the 16-byte loads leave few in
+// flight otherwise; at N = 24 the registers cost a wavefront.
 enum { PIPE_OFF = 0, PIPE_ROTATE = 1, PIPE_TWO = 2 };
 
 // Geometry of one work item: the x-chunk c (x-indices = c mod CH, NP = N/CH of them)
@@ -295,18 +295,21 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
 // directions (icosahedron) 5 are fresh, of 6 (half of them) 3, of 24 6, of the octahedron's 6
 // 3.  The others take the kept values back (the same values: nothing is rounded again)
 // instead of reading the spectrum and combining it anew.  It pays where the values find room in
-// registers or where the x-pass is most of the kernel.  VSS calls, us without / with: 96
-// argon-krypton nodes at N = 32 8657 / 7888, FP64 at N = 32 (8 nodes) 2043 / 1891, at N = 24
-// (20) 1588 / 1413, at N = 16 (60) 780 / 758, FP32 at N = 24 (40) 1243 / 1235; but FP32 at N =
-// 16 (100) 486 / 492 and N = 48 (5) 2401 / 2476.  VHS calls at N = 64: FP32 (2) 4554 / 4027,
-// FP64 (1) 6016 / 5823; FP64 at N = 32 (5, SSP-RK2 step) 1132 / 1100, N = 24 (60) 2038 / 2003; but
-// FP64 at N = 16 (200) 844 / 1140, N = 48 (4) 3327 / 3662, dealiased N = 32 (10) 1998 / 2460, FP32 at N = 24 (63 nodes, DG)
-// 3208 / 3641, N = 16 (300) 583 / 722 (a wavefront per SIMD less) and the packed N = 48 form (7)
-// 2296 / 3022 (two fields' values in private memory; in a place of the workspace per
-// workgroup, 8 nodes of three species, 5.7 / 7.1 ms in the gain).
+// registers or where the x-pass is most of the kernel.  Calls in us, without / with:
+//   VSS: FP32 N = 32 (96 nodes, argon-krypton) 8657 / 7888, N = 24 (40) 1243 / 1235, but
+//     N = 16 (100) 486 / 492 and N = 48 (5) 2401 / 2476; FP64 N = 32 (8) 2043 / 1891,
+//     N = 24 (20) 1588 / 1413, N = 16 (60) 780 / 758;
+//   VHS, N = 64: FP32 (2 nodes) 4554 / 4027, FP64 (1) 6016 / 5823;
+//   VHS, FP64: N = 32 (5, SSP-RK2 step) 1132 / 1100, N = 24 (60) 2038 / 2003, but
+//     N = 16 (200) 844 / 1140 and N = 48 (4) 3327 / 3662;
+//   VHS, FP32: N = 24 (63, DG) 3208 / 3641 and N = 16 (300) 583 / 722 (a wavefront per SIMD
+//     less); dealiased N = 32 (10) 1998 / 2460; the packed N = 48 form (7) 2296 / 3022 (two
+//     fields' values in private memory; in a place of the workspace per workgroup, 8 nodes
+//     of three species, 5.7 / 7.1 ms in the gain).
 template <typename T, int N, int MODE>
 constexpr bool keep_ok() {
-    return MODE == GAIN_VSS ? N < 48 && (N > 16 || sizeof(T) == 8) : MODE == GAIN_REAL && (N == 64 || (sizeof(T) == 8 && (N == 24 || N == 32)));
+    if (MODE == GAIN_VSS) return N < 48 && (N > 16 || sizeof(T) == 8);
+    return MODE == GAIN_REAL && (N == 64 || (sizeof(T) == 8 && (N == 24 || N == 32)));
 }
 template <int NP, typename T>
 __device__ __forceinline__ void keep_x(cx<T>* to, const cx<T>* from) {
