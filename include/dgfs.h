@@ -138,14 +138,20 @@ void dgfs_plan_destroy(dgfs_plan* plan);
 
 /* Bytes of device workspace dgfs_collide/dgfs_collide_pairs need for `batch` nodes
  * processed in one pass.  A smaller workspace (at least the one-node size) makes the
- * call process the batch in slices. */
+ * call process the batch in slices.  dgfs_spread_size bytes of it are optional. */
 dgfs_status dgfs_workspace_size(const dgfs_plan* plan, int64_t batch, size_t* bytes);
+
+/* The bytes by which dgfs_workspace_size(plan, batch), dgfs_relax_workspace_size and the
+ * plan's share of dgfs_slab_workspace_size and dgfs_group_workspace_size exceed what their
+ * calls need: with them the gain of every call of up to `batch` nodes that would leave the
+ * chip idle runs on more of it.  A workspace smaller by this much is accepted by every call
+ * and gives the same result. */
+dgfs_status dgfs_spread_size(const dgfs_plan* plan, int64_t batch, size_t* bytes);
 
 /* Q[b][i] = sum_j Q^{ij}(f[b][i], f[b][j]) for b < batch.
  * f, Q: device arrays [batch][s][N^3] of the plan precision; f and Q must not overlap.
- * workspace: device memory, 256-byte aligned, ws_bytes >= dgfs_workspace_size(plan, 1).
- * (That size may count memory with which the gain of a few nodes runs on more of the chip;
- * a workspace without room for it is accepted too and gives the same result.) */
+ * workspace: device memory, 256-byte aligned, ws_bytes >= dgfs_workspace_size(plan, 1) less
+ * dgfs_spread_size(plan, 1). */
 dgfs_status dgfs_collide(const dgfs_plan* plan, const void* f, void* Q, int64_t batch,
                          void* workspace, size_t ws_bytes, void* stream);
 
@@ -268,7 +274,8 @@ dgfs_status dgfs_slab_workspace_size(const dgfs_slab* slab, int32_t scheme, size
 
 /* Advance f in place by `steps` steps of size dt (forward Euler, or the SSP-RK2 scheme
  * of Sec. 5: f1 = f + dt L(f), f <- f/2 + (f1 + dt L(f1))/2).  workspace: device memory
- * of at least dgfs_slab_workspace_size bytes, 256-byte aligned.  Asynchronous. */
+ * of at least dgfs_slab_workspace_size bytes (less dgfs_spread_size of the plan for the
+ * slab's nodes, if it collides), 256-byte aligned.  Asynchronous. */
 dgfs_status dgfs_slab_step(const dgfs_slab* slab, void* f, double dt, int32_t steps, int32_t scheme,
                            void* workspace, size_t ws_bytes, void* stream);
 
@@ -307,11 +314,14 @@ typedef struct dgfs_group dgfs_group;
 dgfs_status dgfs_group_create(const dgfs_plan* const* plans, int32_t nplans, dgfs_group** out);
 void dgfs_group_destroy(dgfs_group* group);
 
-/* Bytes of one workspace covering batch[k] nodes of every plan k in one pass. */
+/* Bytes of one workspace covering batch[k] nodes of every plan k in one pass, with each
+ * plan's dgfs_spread_size (a plan without nodes counts as one of one node). */
 dgfs_status dgfs_group_workspace_size(const dgfs_group* group, const int64_t* batch, size_t* bytes);
 
 /* For every plan k: Q[k] = collide(plan k, f[k], batch[k]) (same layout as dgfs_collide).
- * The caller's stream waits for all of them.  Asynchronous. */
+ * The caller's stream waits for all of them.  A workspace smaller than
+ * dgfs_group_workspace_size by the plans' dgfs_spread_size is accepted; what it holds beyond
+ * that goes to the plans in order.  Asynchronous. */
 dgfs_status dgfs_group_collide(dgfs_group* group, const void* const* f, void* const* Q,
                                const int64_t* batch, void* workspace, size_t ws_bytes, void* stream);
 

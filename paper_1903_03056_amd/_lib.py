@@ -17,6 +17,7 @@ DGFS_FP32, DGFS_FP64 = 0, 1
 
 EXPORTED = (
     "dgfs_check_problem", "dgfs_pair_prefactor", "dgfs_plan_create", "dgfs_plan_destroy", "dgfs_workspace_size",
+    "dgfs_spread_size",
     "dgfs_collide", "dgfs_collide_static", "dgfs_static_workspace_bytes", "dgfs_collide_timed", "dgfs_collide_pairs", "dgfs_collide_plain", "dgfs_conserve",
     "dgfs_conserve_update", "dgfs_pair_tables", "dgfs_design", "dgfs_interpolation_matrix", "dgfs_kernel_mode",
     "dgfs_status_string", "dgfs_last_error", "dgfs_tile_candidates", "dgfs_group_create", "dgfs_group_destroy",
@@ -83,6 +84,7 @@ def load() -> ctypes.CDLL:
     lib.dgfs_plan_destroy.argtypes = [c_void_p]
     lib.dgfs_plan_destroy.restype = None
     lib.dgfs_workspace_size.argtypes = [c_void_p, c_int64, POINTER(c_size_t)]
+    lib.dgfs_spread_size.argtypes = [c_void_p, c_int64, POINTER(c_size_t)]
     for name in ("dgfs_collide", "dgfs_collide_pairs", "dgfs_collide_plain"):
         getattr(lib, name).argtypes = [c_void_p, c_void_p, c_void_p, c_int64, c_void_p, c_size_t, c_void_p]
     lib.dgfs_collide_timed.argtypes = [c_void_p, c_void_p, c_void_p, c_int64, c_void_p, c_size_t, c_void_p,

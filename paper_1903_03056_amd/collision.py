@@ -183,6 +183,13 @@ class CollisionPlan:
         check(self._lib.dgfs_workspace_size(self._plan, batch, ctypes.byref(n)), "dgfs_workspace_size")
         return n.value
 
+    def spread_bytes(self, batch: int) -> int:
+        """The optional part of workspace_bytes(batch), relax_workspace_bytes(batch) and of a
+        slab's or group's size (dgfs_spread_size)."""
+        n = c_size_t()
+        check(self._lib.dgfs_spread_size(self._plan, batch, ctypes.byref(n)), "dgfs_spread_size")
+        return n.value
+
     def workspace(self, batch: int, device=None, stream=None):
         """A cached device workspace big enough for ``batch`` nodes in one pass, one per
         stream (calls on different streams may run concurrently, each needs its own).

@@ -828,11 +828,33 @@ size_t dgfs_plan::ws_per_node(bool pairs) const {
     return c * size_t(s) + 2 * half * size_t(nslots) + part * classes.size() * size_t(nrho) + prep;
 }
 
+size_t dgfs_plan::ws_required(int64_t batch) const {
+    return std::max(ws_per_node(true) * size_t(batch) + ws_slack(), dgfs::plain_ws_bytes(*this) + 256);
+}
+
+// The most nodes of a call that splits; the dealiased and VSS forms do not.
+static int64_t split_nodes(const dgfs_plan& P) {
+    if (P.inner || P.vss) return 0;
+    return dgfs::split_nodes(P.N, P.precision, P.geo, int(P.classes.size()), P.nrho);
+}
+
 size_t dgfs_plan::ws_split(int64_t nb) const {
+    return nb <= split_nodes(*this) ? detail_align(size_t(nb) * total_dirs * nrho * n3() * elem()) : 0;
+}
+
+size_t dgfs_plan::ws_spread(int64_t batch) const {
+    // The terms grow with the nodes up to the largest call that splits; the nodes that such a
+    // call leaves unused hold part of them.
+    const size_t per = ws_per_node(false);
+    auto beyond = [&](const dgfs_plan& p) {
+        const int64_t nb = std::min(batch, split_nodes(p));
+        const size_t terms = p.ws_split(nb), spare = per * size_t(batch - nb);
+        return terms > spare ? detail_align(terms - spare) : size_t(0);
+    };
+    if (parts.empty()) return beyond(*this);
     size_t most = 0;   // the parts run one after the other in the same memory
-    for (const auto& part : parts) most = std::max(most, part.plan->ws_split(nb));
-    if (!parts.empty() || inner || vss || !dgfs::split_directions(N, precision, geo, int(classes.size()), nrho, nb)) return most;
-    return detail_align(size_t(nb) * total_dirs * nrho * n3() * elem());
+    for (const auto& part : parts) most = std::max(most, beyond(*part.plan));
+    return most;
 }
 
 extern "C" {
@@ -928,8 +950,14 @@ dgfs_status dgfs_workspace_size(const dgfs_plan* plan, int64_t batch, size_t* by
     if (batch < 1) return fail(DGFS_EINVAL, "batch must be >= 1");
     // the pair-resolved mode needs the larger slot set; size for it (and at least what
     // the plain FP64 path needs for one node)
-    *bytes = std::max(plan->ws_per_node(true) * size_t(batch) + plan->ws_slack() + plan->ws_split(batch),
-                      dgfs::plain_ws_bytes(*plan) + 256);
+    *bytes = plan->ws_required(batch) + plan->ws_spread(batch);
+    return DGFS_OK;
+}
+
+dgfs_status dgfs_spread_size(const dgfs_plan* plan, int64_t batch, size_t* bytes) {
+    if (!plan || !bytes) return fail(DGFS_EINVAL, "plan and bytes are required");
+    if (batch < 1) return fail(DGFS_EINVAL, "batch must be >= 1");
+    *bytes = plan->ws_spread(batch);
     return DGFS_OK;
 }
 
@@ -1056,7 +1084,7 @@ dgfs_status dgfs_relax_workspace_size(const dgfs_plan* plan, int64_t batch, int3
     if (batch < 1) return fail(DGFS_EINVAL, "batch must be >= 1");
     if (scheme != DGFS_EULER && scheme != DGFS_SSPRK2) return fail(DGFS_EINVAL, "unknown scheme");
     *bytes = state_bytes(plan, batch) * (scheme == DGFS_SSPRK2 ? 2 : 1) + plan->ws_per_node(false) * size_t(batch) +
-             plan->ws_slack() + plan->ws_split(batch);
+             plan->ws_slack() + plan->ws_spread(batch);
     return DGFS_OK;
 }
 
@@ -1134,14 +1162,12 @@ struct dgfs_group {
     int device = 0;
 };
 
-static size_t group_offset(const dgfs_group* g, const int64_t* batch, size_t k) {
-    size_t off = 0;
-    for (size_t i = 0; i < k; ++i) {
-        size_t b = 0;
-        dgfs_workspace_size(g->plans[i], std::max<int64_t>(batch[i], 1), &b);
-        off += (b + 255) & ~size_t(255);
-    }
-    return off;
+// Bytes of plan k's share of a group workspace: what its call needs, and what lets it spread.
+static size_t group_required(const dgfs_group* g, const int64_t* batch, size_t k) {
+    return detail_align(g->plans[k]->ws_required(std::max<int64_t>(batch[k], 1)));
+}
+static size_t group_spread(const dgfs_group* g, const int64_t* batch, size_t k) {
+    return detail_align(g->plans[k]->ws_spread(std::max<int64_t>(batch[k], 1)));
 }
 
 dgfs_status dgfs_group_create(const dgfs_plan* const* plans, int32_t nplans, dgfs_group** out) {
@@ -1187,7 +1213,8 @@ dgfs_status dgfs_group_workspace_size(const dgfs_group* g, const int64_t* batch,
     if (!g || !batch || !bytes) return fail(DGFS_EINVAL, "group, batch and bytes are required");
     for (size_t k = 0; k < g->plans.size(); ++k)
         if (batch[k] < 0) return fail(DGFS_EINVAL, "batch must be >= 0");
-    *bytes = group_offset(g, batch, g->plans.size());
+    *bytes = 0;
+    for (size_t k = 0; k < g->plans.size(); ++k) *bytes += group_required(g, batch, k) + group_spread(g, batch, k);
     return DGFS_OK;
 }
 
@@ -1195,20 +1222,27 @@ dgfs_status dgfs_group_collide(dgfs_group* g, const void* const* f, void* const*
                                void* ws, size_t ws_bytes, void* stream) {
     if (!g || !f || !Q || !batch || !ws) return fail(DGFS_EINVAL, "group, f, Q, batch and workspace are required");
     size_t need = 0;
-    dgfs_status st = dgfs_group_workspace_size(g, batch, &need);
-    if (st != DGFS_OK) return st;
+    dgfs_status st = DGFS_OK;
+    for (size_t k = 0; k < g->plans.size(); ++k) {
+        if (batch[k] < 0) return fail(DGFS_EINVAL, "batch must be >= 0");
+        need += group_required(g, batch, k);
+    }
     if (ws_bytes < need) return fail(DGFS_ENOMEM, "group workspace too small");
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(DGFS_EINVAL, "workspace must be 256-byte aligned");
     hipStream_t main = static_cast<hipStream_t>(stream);
     if (hipEventRecord(g->fork, main) != hipSuccess) return fail(DGFS_EDEVICE, "hipEventRecord failed");
+    // the plans run side by side, each in its own share: what its call needs, and room to
+    // spread while there is more than all of them need
+    size_t off = 0, surplus = ws_bytes - need;
     for (size_t k = 0; k < g->plans.size(); ++k) {
+        const size_t want = group_spread(g, batch, k), extra = want <= surplus ? want : 0;
+        const size_t at = off, b = group_required(g, batch, k) + extra;
+        surplus -= extra;
+        off += b;
         if (batch[k] == 0) continue;
         if (hipStreamWaitEvent(g->streams[k], g->fork, 0) != hipSuccess)
             return fail(DGFS_EDEVICE, "hipStreamWaitEvent failed");
-        const size_t off = group_offset(g, batch, k);
-        size_t b = 0;
-        dgfs_workspace_size(g->plans[k], batch[k], &b);
-        st = collide_impl(g->plans[k], f[k], Q[k], batch[k], static_cast<char*>(ws) + off, b, g->streams[k], false,
+        st = collide_impl(g->plans[k], f[k], Q[k], batch[k], static_cast<char*>(ws) + at, b, g->streams[k], false,
                           nullptr);
         if (st != DGFS_OK) return st;
         if (hipEventRecord(g->join[k], g->streams[k]) != hipSuccess ||

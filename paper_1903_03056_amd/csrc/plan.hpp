@@ -25,7 +25,7 @@ struct GainGeometry {
 // The default: the first compiled geometry, skipping the matrix-core ones (CZ = 0: FP32
 // VHS plans of the circular form) unless matrix_ok.
 bool gain_geometry(int N, int precision, GainGeometry* g, bool matrix_ok = true);
-// Whether a call of nb nodes spreads the directions of its gain items over the chip, one
+// A call of few nodes spreads the directions of its gain items over the chip, one
 // workgroup per (item, direction), and sums them in a second kernel (gain.hpp).  An item runs
 // up to M directions one after the other, so a call whose items do not fill the CUs takes M
 // directions' time whatever its size; the split costs a pass over the terms (one value per
@@ -35,9 +35,10 @@ bool gain_geometry(int N, int precision, GainGeometry* g, bool matrix_ok = true)
 //   FP64 N = 16 (two): 24 71 / 42, 360 150 / 116, 576 149 / 160;  FP64 N = 24 (two): 324 200 / 239;
 //   FP64 N = 32 (one): 384 341 / 302, 576 442 / 456.
 // Above N = 32 a node has more items than the chip has CUs.
-inline bool split_directions(int N, int precision, const GainGeometry& geo, int ncls, int nrho, int64_t nb) {
+// Returns the most nodes of a call that does (0: none).
+inline int64_t split_nodes(int N, int precision, const GainGeometry& geo, int ncls, int nrho) {
     const int64_t most = precision == 0 && N <= 24 ? 960 : N == 24 ? 256 : 400;   // precision 0: FP32
-    return N <= 32 && geo.CZ > 0 && nb * ncls * nrho * geo.CH <= most;
+    return N <= 32 && geo.CZ > 0 ? most / (int64_t(ncls) * nrho * geo.CH) : 0;
 }
 // Bytes per (node, species) of the matrix-core gain's prepared input (N = 32): f split into
 // FP16 hi and lo, the alternating x-sum plane split likewise, and 64 FP32 scalars.
@@ -127,9 +128,14 @@ struct dgfs_plan {
     // workspace bytes per node, and the alignment slack added once per call
     size_t ws_per_node(bool pairs) const;
     size_t ws_slack() const { return parts.empty() ? 4 * 256 : 12 * 256; }
+    // what a pass over `batch` nodes needs in either mode, and the plain FP64 path for one node
+    size_t ws_required(int64_t batch) const;
     // bytes beyond those with which a call of nb nodes spreads its gain directions over the
     // chip (gain.hpp); 0 where it does not
     size_t ws_split(int64_t nb) const;
+    // bytes beyond ws_required(batch) with which every call of up to `batch` nodes finds room
+    // for that
+    size_t ws_spread(int64_t batch) const;
 };
 
 namespace dgfs {

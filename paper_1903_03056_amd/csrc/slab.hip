@@ -384,12 +384,13 @@ dgfs_status dgfs_slab_step(const dgfs_slab* slab, void* f, double dt, int32_t st
     if (!f || !workspace) return dgfs::set_error(DGFS_EINVAL, "f and workspace are required");
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
         return dgfs::set_error(DGFS_EINVAL, "workspace must be 256-byte aligned");
-    size_t need = 0;
-    dgfs_status rc = dgfs_slab_workspace_size(slab, scheme, &need);
-    if (rc != DGFS_OK) return rc;
-    if (ws_bytes < need) return dgfs::set_error(DGFS_ENOMEM, "workspace smaller than dgfs_slab_workspace_size");
     const dgfs_slab& S = *slab;
     const size_t sb = state_bytes(S);
+    const size_t need = sb * (scheme == DGFS_SSPRK2 ? 3 : 2) + kPartBytes +
+                        (S.desc.collide ? S.plan->ws_required(S.nodes) : 0);
+    if (ws_bytes < need)
+        return dgfs::set_error(DGFS_ENOMEM, "workspace smaller than dgfs_slab_workspace_size less dgfs_spread_size");
+    dgfs_status rc = DGFS_OK;
     char* w = static_cast<char*>(workspace);
     void* f1 = w;
     void* f2 = scheme == DGFS_SSPRK2 ? w + sb : nullptr;

@@ -1,0 +1,106 @@
+"""What a workspace has to hold: the part of its size with which small calls spread over the
+chip is optional in every entry point, and the rest grows with the batch, so that a workspace
+of a larger batch serves every smaller one.  Results are the same bit for bit either way."""
+import numpy as np
+import pytest
+
+from synth import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+MASSES, L = (1.0, 2.0), 6.0
+
+
+def _plan(N, M=12, nrho=4, precision="f32", masses=MASSES, L=L, **kw):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_03056_amd import CollisionPlan
+    return CollisionPlan(masses, N, L, M, nrho, omega=0.74, precision=precision, **kw)
+
+
+def _state(plan, batch, seed=41):
+    f = I.draw_bimaxwellian_batch(np.random.default_rng(seed), batch, plan.s, plan.N, plan.L_species, plan.masses,
+                                  noise=1e-2)
+    return torch.tensor(f, dtype=plan.dtype, device="cuda")
+
+
+def _bytes(n):
+    return torch.empty(n, dtype=torch.uint8, device="cuda")
+
+
+def _per_node(plan):
+    """Bytes per node of a large call, which has no optional part."""
+    return (plan.workspace_bytes(20000) - plan.workspace_bytes(10000)) // 10000
+
+
+def _group_bytes(plans, batches):
+    """The bytes that a group's calls need, each plan's share a multiple of 256."""
+    return sum((_per_node(p) * b + 1024 + 255) // 256 * 256 for p, b in zip(plans, batches))
+
+
+@pytest.mark.parametrize("N,M,nrho,precision,masses,L", [
+    (16, 12, 8, "f32", MASSES, 6.0), (24, 12, 12, "f32", (1.0, 2.0, 4.0), 6.0), (16, 6, 4, "f64", (1.0,), 6.0),
+    (16, 12, 5, "f32", MASSES, (6.0, 4.0)), (32, 12, 16, "f32", MASSES, 6.0)])
+def test_sizes_grow_with_the_batch(N, M, nrho, precision, masses, L):
+    print(f"[case] workspace sizes N={N} M={M} {precision} s={len(masses)} L={L}", flush=True)
+    plan = _plan(N, M, nrho, precision, masses, L)
+    for size in (plan.workspace_bytes, plan.relax_workspace_bytes):
+        sizes = [size(b) for b in range(1, 200)]
+        assert sizes == sorted(sizes)
+    assert plan.spread_bytes(10000) == 0
+    # the rest: per node and alignment, and at least what the plain path needs for one node
+    need = [plan.workspace_bytes(b) - plan.spread_bytes(b) for b in range(1, 200)]
+    fixed = need[-1] - 199 * _per_node(plan)
+    assert 0 < fixed <= 12 * 256
+    assert need == [max(need[0], _per_node(plan) * b + fixed) for b in range(1, 200)]
+
+
+def test_group_takes_a_workspace_without_the_optional_part():
+    print("[case] group workspaces", flush=True)
+    from paper_1903_03056_amd import CollisionGroup
+    from paper_1903_03056_amd._lib import DgfsError
+    plans = [_plan(24), _plan(16), _plan(16, nrho=3)]
+    batches = (3, 5, 2)
+    group = CollisionGroup(plans)
+    fs = [_state(p, b) for p, b in zip(plans, batches)]
+    want = [p.collide(f) for p, f in zip(plans, fs)]
+    assert all(p.spread_bytes(b) > 0 for p, b in zip(plans, batches))
+    need, full = _group_bytes(plans, batches), group.workspace_bytes(batches)
+    # none of the optional part, a part of it, all of it, and the size for a larger batch
+    for n in (need, need + plans[0].spread_bytes(3) + 256, full, _group_bytes(plans, (90, 90, 90))):
+        print(f"[step] {n} bytes", flush=True)
+        ws = _bytes(n)
+        for q, w in zip(group.collide(fs, workspace=ws), want):
+            assert torch.equal(q, w)
+        graph, outs = group.capture(fs, workspace=ws)
+        for _ in range(2):
+            for q in outs:
+                q.zero_()
+            torch.cuda.synchronize()
+            graph.launch()
+            graph.stream.synchronize()
+            assert all(torch.equal(q, w) for q, w in zip(outs, want))
+    with pytest.raises(DgfsError):
+        group.collide(fs, workspace=_bytes(need - 256))
+
+
+@pytest.mark.parametrize("scheme", ["euler", "ssprk2"])
+def test_slab_takes_a_workspace_without_the_optional_part(scheme):
+    print(f"[case] slab workspaces {scheme}", flush=True)
+    from paper_1903_03056_amd import Slab
+    from paper_1903_03056_amd._lib import DgfsError
+    plan = _plan(16)
+    wall = [dict(kind="wall", u=(0.0, u, 0.0), T=1.0) for u in (-0.3, 0.3)]
+    slab = Slab(plan, 0.0, 1.0, 4, 3, *wall)
+    f = _state(plan, 12)
+    full, spread = slab.workspace_bytes(scheme), plan.spread_bytes(12)
+    assert spread > 0
+    want = slab.step(f.clone(), 2e-4, 2, scheme=scheme)
+    assert torch.equal(slab.step(f.clone(), 2e-4, 2, scheme=scheme, workspace=_bytes(full - spread)), want)
+    with pytest.raises(DgfsError):
+        slab.step(f.clone(), 2e-4, 1, scheme=scheme, workspace=_bytes(full - spread - 256))
+    # a slab without collisions has no optional part
+    free = Slab(plan, 0.0, 1.0, 4, 3, *wall, collide=False)
+    free.step(f.clone(), 2e-4, 1, scheme=scheme, workspace=_bytes(free.workspace_bytes(scheme)))
