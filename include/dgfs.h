@@ -144,8 +144,8 @@ dgfs_status dgfs_workspace_size(const dgfs_plan* plan, int64_t batch, size_t* by
 /* The bytes by which dgfs_workspace_size(plan, batch), dgfs_relax_workspace_size and the
  * plan's share of dgfs_slab_workspace_size and dgfs_group_workspace_size exceed what their
  * calls need: with them the gain of every call of up to `batch` nodes that would leave the
- * chip idle runs on more of it.  A workspace smaller by this much is accepted by every call
- * and gives the same result. */
+ * chip idle runs on more of it.  At most 256 MiB.  A workspace smaller by this much is
+ * accepted by every call and gives the same result. */
 dgfs_status dgfs_spread_size(const dgfs_plan* plan, int64_t batch, size_t* bytes);
 
 /* Q[b][i] = sum_j Q^{ij}(f[b][i], f[b][j]) for b < batch.

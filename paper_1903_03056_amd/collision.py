@@ -185,7 +185,7 @@ class CollisionPlan:
 
     def spread_bytes(self, batch: int) -> int:
         """The optional part of workspace_bytes(batch), relax_workspace_bytes(batch) and of a
-        slab's or group's size (dgfs_spread_size)."""
+        slab's or group's size (dgfs_spread_size); at most 256 MiB."""
         n = c_size_t()
         check(self._lib.dgfs_spread_size(self._plan, batch, ctypes.byref(n)), "dgfs_spread_size")
         return n.value

@@ -832,14 +832,19 @@ size_t dgfs_plan::ws_required(int64_t batch) const {
     return std::max(ws_per_node(true) * size_t(batch) + ws_slack(), dgfs::plain_ws_bytes(*this) + 256);
 }
 
-// The most nodes of a call that splits; the dealiased and VSS forms do not.
+// Bytes of a node's terms for one radial point.
+static size_t split_point(const dgfs_plan& P) { return size_t(P.total_dirs) * P.n3() * P.elem(); }
+
+// The most nodes of a call that splits: those whose terms fit for one radial point at least; the
+// dealiased and VSS forms do not split.
 static int64_t split_nodes(const dgfs_plan& P) {
     if (P.inner || P.vss) return 0;
-    return dgfs::split_nodes(P.N, P.precision, P.geo, int(P.classes.size()), P.nrho);
+    return std::min(dgfs::split_nodes(P.N, P.precision, P.geo, int(P.classes.size()), P.nrho),
+                    int64_t(dgfs::split_bytes / split_point(P)));
 }
 
 size_t dgfs_plan::ws_split(int64_t nb) const {
-    return nb <= split_nodes(*this) ? detail_align(size_t(nb) * total_dirs * nrho * n3() * elem()) : 0;
+    return nb <= split_nodes(*this) ? std::min(detail_align(size_t(nb) * nrho * split_point(*this)), dgfs::split_bytes) : 0;
 }
 
 size_t dgfs_plan::ws_spread(int64_t batch) const {

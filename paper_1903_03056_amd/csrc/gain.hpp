@@ -119,8 +119,9 @@ struct GainArgs {
     const T* wdir;      // [ncls]
     const int* ord;     // [ncls] classes, most directions first
     const int* xs;      // [dirs]  1: the direction before it in its class has the same sigma_x
-    T* D;               // GAIN_TERMS: [nb][dirs][nrho][CH][N/CZ][threads]  Re(A B) of one direction
+    T* D;               // GAIN_TERMS: [nb][dirs][nq][CH][N/CZ][threads]  Re(A B) of one direction
     int s, ncls, nrho, nb, tdirs;
+    int q0 = 0, nq = 0; // GAIN_TERMS and gain_sum_kernel: the radial points q0 .. q0 + nq - 1
 };
 
 // out[j] = X[CZ j + CZI] of the length-N DFT (sign SIGN) of the sequence
@@ -902,12 +903,13 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
     __shared__ cx<T> buf[K::LDS + ((PACK && pack_ok<T, N, CH, CZ>()) ? K::LINES : 0)];
     int b, item;
     // the items of a node: classes, or with GAIN_TERMS the directions of all classes
-    if (!gain_item<1>(blockIdx.x, a.nb, MODE == GAIN_TERMS ? a.tdirs : a.ncls, a.nrho * CH,
+    const int nq = MODE == GAIN_TERMS ? a.nq : a.nrho;
+    if (!gain_item<1>(blockIdx.x, a.nb, MODE == GAIN_TERMS ? a.tdirs : a.ncls, nq * CH,
                       MODE == GAIN_TERMS ? nullptr : a.ord, b, item)) return;
     const int c = item % CH;
     item /= CH;
-    const int q = item % a.nrho;
-    int cl = item / a.nrho, dir = 0;
+    const int q = MODE == GAIN_TERMS ? a.q0 + item % nq : item % nq;
+    int cl = item / nq, dir = 0;
     if constexpr (MODE == GAIN_TERMS) {
         for (dir = cl, cl = 0; dir >= a.cls[4 * cl + 2]; ++cl) dir -= a.cls[4 * cl + 2];
     }
@@ -1035,7 +1037,7 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
         }
     } else if constexpr (MODE == GAIN_TERMS) {
         direction(dir, S);
-        T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + dir) * a.nrho + q) * CH + c) * int64_t(K::NT * K::NS) + tid;
+        T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + dir) * nq + q - a.q0) * CH + c) * int64_t(K::NT * K::NS) + tid;
 #pragma unroll
         for (int j = 0; j < K::NS; ++j) Dq[j * K::NT] = S[j];
         return;
@@ -1063,11 +1065,11 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_sum_kernel(Gai
     using K = GainK<T, N, CH, CZ>;
     __shared__ cx<T> buf[K::LDS];
     int b, item;
-    if (!gain_item<1>(blockIdx.x, a.nb, a.ncls, a.nrho * CH, a.ord, b, item)) return;
+    if (!gain_item<1>(blockIdx.x, a.nb, a.ncls, a.nq * CH, a.ord, b, item)) return;
     const int c = item % CH;
     item /= CH;
-    const int q = item % a.nrho;
-    const int cl = item / a.nrho;
+    const int qt = item % a.nq, q = a.q0 + qt;
+    const int cl = item / a.nq;
     const int ndir = a.cls[4 * cl + 2], doff = a.cls[4 * cl + 3];
     const T w = a.wdir[cl];
     const int tid = threadIdx.x;
@@ -1078,7 +1080,7 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_sum_kernel(Gai
     for (int j = 0; j < K::NS; ++j) S[j] = T(0);
 #pragma unroll 2
     for (int d = 0; d < ndir; ++d) {
-        const T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + d) * a.nrho + q) * CH + c) * int64_t(K::NT * K::NS) + tid;
+        const T* Dq = a.D + (((int64_t(b) * a.tdirs + doff + d) * a.nq + qt) * CH + c) * int64_t(K::NT * K::NS) + tid;
 #pragma unroll
         for (int j = 0; j < K::NS; ++j) S[j] = fma(w, Dq[j * K::NT], S[j]);
     }
@@ -1746,7 +1748,7 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, Scratch ws, b
         if ((e = launch_gain_mfma32(p, f, P, prep, nb, st)) != hipSuccess) return e;
     } else {
         const int64_t ipn = int64_t(ncls) * p.nrho * CH;
-        const dim3 grid(gain_groups(nb, ipn)), block(GainK<T, N, CH, CZ>::NT);
+        const dim3 block(GainK<T, N, CH, CZ>::NT);
         bool split = false;
         if constexpr (!VSS && N <= 32) {
             // the terms follow the loss spectra, where the caller's workspace reaches so far
@@ -1756,12 +1758,19 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, Scratch ws, b
             if (bytes != 0 && used <= ws.bytes && bytes <= ws.bytes - used) {
                 split = true;
                 ga.D = reinterpret_cast<T*>(terms);
-                gain_kernel<T, N, CH, CZ, PIPE, PACK, GAIN_TERMS>
-                    <<<dim3(gain_groups(nb, int64_t(p.total_dirs) * p.nrho * CH)), block, 0, st>>>(ga);
-                gain_sum_kernel<T, N, CH, CZ><<<grid, block, 0, st>>>(ga);
+                // as many radial points at a time as the memory holds, in equal groups
+                const int fit = int(std::min<size_t>(p.nrho, bytes / (sizeof(T) * N3 * nb * p.total_dirs)));
+                const int groups = (p.nrho + fit - 1) / fit, per = (p.nrho + groups - 1) / groups;
+                for (ga.q0 = 0; ga.q0 < p.nrho; ga.q0 += per) {
+                    ga.nq = std::min(per, p.nrho - ga.q0);
+                    gain_kernel<T, N, CH, CZ, PIPE, PACK, GAIN_TERMS>
+                        <<<dim3(gain_groups(nb, int64_t(p.total_dirs) * ga.nq * CH)), block, 0, st>>>(ga);
+                    gain_sum_kernel<T, N, CH, CZ>
+                        <<<dim3(gain_groups(nb, int64_t(ncls) * ga.nq * CH)), block, 0, st>>>(ga);
+                }
             }
         }
-        if (!split) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<grid, block, 0, st>>>(ga);
+        if (!split) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<dim3(gain_groups(nb, ipn)), block, 0, st>>>(ga);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if constexpr (VSS) {

@@ -40,6 +40,11 @@ inline int64_t split_nodes(int N, int precision, const GainGeometry& geo, int nc
     const int64_t most = precision == 0 && N <= 24 ? 960 : N == 24 ? 256 : 400;   // precision 0: FP32
     return N <= 32 && geo.CZ > 0 ? most / (int64_t(ncls) * nrho * geo.CH) : 0;
 }
+// The most bytes of terms held at once: a call with more spreads the radial points in groups,
+// one pair of launches each, of as many as fit.  Each group still has more workgroups than the
+// chip runs together (256 MiB are 1024 FP64 or 2048 FP32 fields at N = 32), so the groups cost
+// launches alone.
+constexpr size_t split_bytes = size_t(256) << 20;
 // Bytes per (node, species) of the matrix-core gain's prepared input (N = 32): f split into
 // FP16 hi and lo, the alternating x-sum plane split likewise, and 64 FP32 scalars.
 constexpr size_t mfma_prep_bytes = (2 * 32768 + 2048) * 2 + 64 * 4;
@@ -131,7 +136,7 @@ struct dgfs_plan {
     // what a pass over `batch` nodes needs in either mode, and the plain FP64 path for one node
     size_t ws_required(int64_t batch) const;
     // bytes beyond those with which a call of nb nodes spreads its gain directions over the
-    // chip (gain.hpp); 0 where it does not
+    // chip (gain.hpp), at most dgfs::split_bytes; 0 where it does not
     size_t ws_split(int64_t nb) const;
     // bytes beyond ws_required(batch) with which every call of up to `batch` nodes finds room
     // for that

@@ -104,3 +104,20 @@ def test_slab_takes_a_workspace_without_the_optional_part(scheme):
     # a slab without collisions has no optional part
     free = Slab(plan, 0.0, 1.0, 4, 3, *wall, collide=False)
     free.step(f.clone(), 2e-4, 1, scheme=scheme, workspace=_bytes(free.workspace_bytes(scheme)))
+
+
+@pytest.mark.parametrize("N,M,nrho,precision,masses,batch,tile", [
+    (32, 24, 25, "f64", MASSES, 1, None),          # 629 MB of terms: three groups of radial points
+    (24, 24, 12, "f32", (1.0,), 26, None),         # 414 MB: two groups
+    (32, 24, 1, "f32", (1.0,), 85, (2, 1)),        # 267 MB for the one point: the most that fit
+    (32, 24, 1, "f32", (1.0,), 86, (2, 1))])       # one node more: no split
+def test_the_optional_part_is_bounded(N, M, nrho, precision, masses, batch, tile):
+    print(f"[case] spread bytes N={N} M={M} nrho={nrho} {precision} batch {batch}", flush=True)
+    plan = _plan(N, M, nrho, precision, masses, tile=tile)
+    assert max(plan.spread_bytes(b) for b in range(1, 400)) <= 256 << 20
+    assert plan.spread_bytes(1) > 0
+    f = _state(plan, min(batch, 3))[torch.arange(batch) % 3].contiguous()
+    need = plan.workspace_bytes(batch) - plan.spread_bytes(batch)
+    Q = plan.collide(f, workspace=_bytes(need + (256 << 20)))
+    assert torch.equal(plan.collide(f, workspace=_bytes(need)), Q)
+    assert torch.isfinite(Q).all() and float(Q.abs().max()) > 0
