@@ -835,16 +835,33 @@ size_t dgfs_plan::ws_required(int64_t batch) const {
 // Bytes of a node's terms for one radial point.
 static size_t split_point(const dgfs_plan& P) { return size_t(P.total_dirs) * P.n3() * P.elem(); }
 
-// The most nodes of a call that splits: those whose terms fit for one radial point at least; the
-// dealiased and VSS forms do not split.
+// The most nodes of a call that may split: those whose terms fit for one radial point at least;
+// the dealiased and VSS forms do not split.
 static int64_t split_nodes(const dgfs_plan& P) {
-    if (P.inner || P.vss) return 0;
-    return std::min(dgfs::split_nodes(P.N, P.precision, P.geo, int(P.classes.size()), P.nrho),
+    if (P.inner || P.vss || P.classes.empty()) return 0;
+    int longest = 0;
+    for (const auto& c : P.classes) longest = std::max(longest, c.ndir);
+    const dgfs::SplitRule rule = dgfs::split_rule(P.N, P.precision, P.geo);
+    return std::min(int64_t(rule.most) * (rule.single ? 2 : 1) * longest / (int64_t(P.nrho) * P.geo.CH * P.total_dirs),
                     int64_t(dgfs::split_bytes / split_point(P)));
 }
 
+// Whether a call of nb nodes splits (plan.hpp, split_rule).
+static bool splits(const dgfs_plan& P, int64_t nb) {
+    if (nb < 1 || nb > split_nodes(P)) return false;
+    int longest = 0;
+    bool alike = true;   // classes of one length
+    for (const auto& c : P.classes) longest = std::max(longest, c.ndir);
+    for (const auto& c : P.classes) alike = alike && c.ndir == longest;
+    const dgfs::SplitRule rule = dgfs::split_rule(P.N, P.precision, P.geo);
+    const double n = double(nb) * P.nrho * P.geo.CH * P.total_dirs / longest;
+    // rounds of the longest class's directions; classes of half its length fill halves of one
+    const double rounds = !rule.single ? 1.0 : alike ? std::ceil(n / 256.0) : std::max(1.0, std::ceil(n / 128.0) / 2.0);
+    return n <= rule.most * std::min(rounds, 2.0);
+}
+
 size_t dgfs_plan::ws_split(int64_t nb) const {
-    return nb <= split_nodes(*this) ? std::min(detail_align(size_t(nb) * nrho * split_point(*this)), dgfs::split_bytes) : 0;
+    return splits(*this, nb) ? std::min(detail_align(size_t(nb) * nrho * split_point(*this)), dgfs::split_bytes) : 0;
 }
 
 size_t dgfs_plan::ws_spread(int64_t batch) const {
@@ -852,7 +869,8 @@ size_t dgfs_plan::ws_spread(int64_t batch) const {
     // call leaves unused hold part of them.
     const size_t per = ws_per_node(false);
     auto beyond = [&](const dgfs_plan& p) {
-        const int64_t nb = std::min(batch, split_nodes(p));
+        int64_t nb = std::min(batch, split_nodes(p));
+        while (nb > 0 && !splits(p, nb)) --nb;
         const size_t terms = p.ws_split(nb), spare = per * size_t(batch - nb);
         return terms > spare ? detail_align(terms - spare) : size_t(0);
     };

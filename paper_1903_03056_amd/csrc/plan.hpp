@@ -27,23 +27,50 @@ struct GainGeometry {
 bool gain_geometry(int N, int precision, GainGeometry* g, bool matrix_ok = true);
 // A call of few nodes spreads the directions of its gain items over the chip, one
 // workgroup per (item, direction), and sums them in a second kernel (gain.hpp).  An item runs
-// up to M directions one after the other, so a call whose items do not fill the CUs takes M
-// directions' time whatever its size; the split costs a pass over the terms (one value per
-// point and direction) in memory.  Calls in us, together / split, by items:
-//   FP32 N = 24 (four workgroups to a CU): 324 148 / 89, 432 159 / 115, 648 172 / 134, 972 186 / 180;
-//   FP32 N = 16 (four): 360 101 / 71, 576 104 / 90, 960 129 / 126;
-//   FP64 N = 16 (two): 24 71 / 42, 360 150 / 116, 576 149 / 160;  FP64 N = 24 (two): 324 200 / 239;
-//   FP64 N = 32 (one): 384 341 / 302, 576 442 / 456.
-// Above N = 32 a node has more items than the chip has CUs.
-// Returns the most nodes of a call that does (0: none).
-inline int64_t split_nodes(int N, int precision, const GainGeometry& geo, int ncls, int nrho) {
-    const int64_t most = precision == 0 && N <= 24 ? 960 : N == 24 ? 256 : 400;   // precision 0: FP32
-    return N <= 32 && geo.CZ > 0 ? most / (int64_t(ncls) * nrho * geo.CH) : 0;
+// its class's directions one after the other, so a call whose items do not fill the chip takes
+// the longest class's time whatever its size; the split takes the time of all directions over
+// the chip, about 1.5 times theirs in full rounds (no kept x-transforms, and the terms, one
+// value per point and direction, go through memory).  So what counts is the call's items in
+// units of the longest class's, n = nb nrho CH dirs / longest, against the workgroups that the
+// chip runs together: `most` is where the two forms cost the same.  With one workgroup per CU
+// (`single`) the unsplit form takes whole rounds of 256, and just past the first one the split
+// is ahead again, up to 2 most.  Calls in us, together / split, by n (one species, M = 12 unless
+// said; two species have classes of two lengths):
+//   FP32 N = 16 (1,1): 248 51/44, 448 60/59, 848 84/88; two species 560 119/108, 672 122/121;
+//     M = 24 600 198/184, 848 229/254, 1000 233/293;
+//   FP32 N = 24 (3,1): 288 83/66, 612 107/100, 684 108/108, 864 116/126; two species 576 175/157;
+//     M = 24 612 322/299, 864 347/393;  (3,2): 360 76/75, 504 79/90, 612 110/103, 864 133/132,
+//     two species 576 175/166;  (3,4): 360 84/83, 504 87/101;  (3,3): 360 110/88, 864 201/166;
+//     (1,1) single: 204 115/114, 252 118/131, 300 202/168, 504 208/236;
+//   FP32 N = 32 (2,1) single: 96 118/95, 160 121/115, 192 123/132, 256 126/152, 288 211/180,
+//     384 211/217; two species 128 208/164, 192 216/219, 256 221/271; M = 24 160 365/323,
+//     256 370/490;  (4,1): 320 134/121, 384 135/134, 448 137/149;  (4,2): 384 170/131;
+//   FP64 N = 16 (1,1): 200 66/61, 352 89/88, 400 89/94; two species 272 129/116, 336 130/135;
+//     M = 24 304 253/216, 400 255/276;
+//   FP64 N = 24 (3,2) single: 108 77/69, 144 79/77, 216 81/97, 288 136/120, 360 139/141; two
+//     species 144 127/118, 216 142/160; M = 24 144 202/193, 216 204/263;
+//   FP64 N = 32 (4,2) single: 128 127/103, 192 137/136, 256 139/157, 320 234/200, 448 233/253;
+//     two species 128 232/174, 256 248/277; M = 24 128 351/278, 192 366/403, 320 702/627.
+// Above N = 32 the split is not compiled: a two-species node fills the chip (N = 48: 432 items at
+// 24 radial points; N = 64: 16 or 32 chunks of each), one species at N = 48 does not (72 to 150
+// items) and runs its directions one after the other.
+struct SplitRule {
+    int most;
+    bool single;
+};
+inline SplitRule split_rule(int N, int precision, const GainGeometry& geo) {
+    const int g = 10 * geo.CH + geo.CZ;
+    if (N > 32 || geo.CZ == 0) return {0, false};
+    if (precision != 0) return N == 16 ? SplitRule{320, false} : N == 24 ? SplitRule{150, true} : SplitRule{192, true};
+    if (N == 16) return {g == 11 ? 600 : g == 21 ? 900 : 960, false};
+    if (N == 24) return g == 11 ? SplitRule{240, true} : SplitRule{g == 34 ? 380 : g == 33 ? 960 : 640, false};
+    return g == 21 ? SplitRule{160, true} : SplitRule{400, false};
 }
 // The most bytes of terms held at once: a call with more spreads the radial points in groups,
 // one pair of launches each, of as many as fit.  Each group still has more workgroups than the
 // chip runs together (256 MiB are 1024 FP64 or 2048 FP32 fields at N = 32), so the groups cost
-// launches alone.
+// launches alone: three FP64 nodes at N = 32, M = 24 (302 MB) 400 us in one group, 392 in two;
+// 17 FP32 nodes at N = 24, M = 24 (271 MB) 287 and 294 us.
 constexpr size_t split_bytes = size_t(256) << 20;
 // Bytes per (node, species) of the matrix-core gain's prepared input (N = 32): f split into
 // FP16 hi and lo, the alternating x-sum plane split likewise, and 64 FP32 scalars.

@@ -1,5 +1,5 @@
 """How the gain's work items are dealt to the chip: whole nodes per XCD for every eight
-nodes, the items of the last nb % 8 nodes over all XCDs; in small calls one workgroup per direction (N = 16 here up to 44
+nodes, the items of the last nb % 8 nodes over all XCDs; in small calls one workgroup per direction (N = 16 here up to 53
 nodes, N = 24 up to 35).  At the edges of those rules every node's result is its result alone,
 bit for bit, and the oracle's; so it is where the workspace has no room for the split.
 
@@ -41,3 +41,27 @@ def test_every_node_at_the_edges_of_the_dealing(N, precision, batch):
     err = float(np.max(np.abs(got - ref).reshape(2, -1).max(1) / np.abs(ref).reshape(2, -1).max(1)))
     print(f"relative L-inf {err:.3e}", flush=True)
     assert err <= (1e-12 if precision == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("N,precision,tile,s,M,nrho,batches", [
+    (16, "f64", None, 2, 6, 3, (53, 54)), (24, "f32", (3, 1), 1, 12, 12, (17, 18)),
+    (24, "f64", None, 1, 12, 12, (4, 5, 8, 9)), (32, "f64", None, 1, 12, 16, (3, 4, 5, 7)),
+    (32, "f64", None, 2, 12, 16, (1, 2)), (32, "f32", (2, 1), 1, 24, 16, (5, 6, 9, 11)),
+    (32, "f32", (4, 2), 2, 12, 16, (3,)), (16, "f32", (2, 1), 3, 12, 4, (5,)), (24, "f32", (3, 4), 2, 6, 4, (3,))])
+def test_split_calls_equal_whole_ones(N, precision, tile, s, M, nrho, batches):
+    """On both sides of the limits, with whole rounds of one workgroup per CU between them: with
+    room for the split and without it, and a node in a batch and alone, bit for bit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_03056_amd import CollisionPlan
+    masses, L = (1.0, 2.0, 4.0)[:s], 6.0
+    plan = CollisionPlan(masses, N, L, M, nrho, omega=0.74, precision=precision, tile=tile)
+    f = I.draw_bimaxwellian_batch(np.random.default_rng(67), max(batches), s, N, L, masses, noise=1e-2)
+    ft = torch.tensor(f, dtype=plan.dtype, device="cuda")
+    for batch in batches:
+        print(f"[case] split N={N} {precision} {tile} s={s} M={M} batch {batch}", flush=True)
+        Q = plan.collide(ft[:batch])
+        least = plan.workspace_bytes(batch) - plan.spread_bytes(batch)
+        assert torch.equal(plan.collide(ft[:batch], workspace=torch.empty(least, dtype=torch.uint8, device="cuda")), Q)
+        for b in (0, batch - 1):
+            assert torch.equal(plan.collide(ft[b:b + 1].contiguous())[0], Q[b]), b

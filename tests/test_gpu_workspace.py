@@ -107,10 +107,10 @@ def test_slab_takes_a_workspace_without_the_optional_part(scheme):
 
 
 @pytest.mark.parametrize("N,M,nrho,precision,masses,batch,tile", [
-    (32, 24, 25, "f64", MASSES, 1, None),          # 629 MB of terms: three groups of radial points
-    (24, 24, 12, "f32", (1.0,), 26, None),         # 414 MB: two groups
-    (32, 24, 1, "f32", (1.0,), 85, (2, 1)),        # 267 MB for the one point: the most that fit
-    (32, 24, 1, "f32", (1.0,), 86, (2, 1))])       # one node more: no split
+    (32, 24, 16, "f64", (1.0,), 3, None),          # 302 MB of terms: two groups of radial points
+    (24, 24, 12, "f32", (1.0,), 17, None),         # 271 MB: two groups
+    (32, 24, 1, "f32", (1.0,), 85, (4, 2)),        # 267 MB for the one point: the most that fit
+    (32, 24, 1, "f32", (1.0,), 86, (4, 2))])       # one node more: no split
 def test_the_optional_part_is_bounded(N, M, nrho, precision, masses, batch, tile):
     print(f"[case] spread bytes N={N} M={M} nrho={nrho} {precision} batch {batch}", flush=True)
     plan = _plan(N, M, nrho, precision, masses, tile=tile)
