@@ -17,8 +17,10 @@ Scheduling:
   Requests join and leave at every step (continuous batching), and the pools' streams
   overlap on the device.
 * Admission is in arrival order and bounded by an HBM budget: a request is admitted only
-  if the bytes its pool would hold afterwards (state, results, workspace) fit.  A request
-  that does not fit waits (it is deferred, never dropped) until retirements free memory.
+  if the bytes its pool would hold afterwards (state, results, workspace) fit, with the
+  workspace's optional part (with which small batches spread over the chip) or else without
+  it.  A request that does not fit waits (it is deferred, never dropped) until retirements
+  free memory.
 * Latency is arrival -> the host seeing the completion event of the request's last step.
 
 The device side is behind a small backend interface (``DeviceBackend``) so that the
@@ -169,20 +171,25 @@ class DevicePool:
         self.event = None
         self.f = self.Q = self.ws = None
         self.cap = 0
+        self.spread = True         # the workspace's optional part is allocated (resize)
         self.peak_cap = 0          # largest slot capacity the pool has held
         self._staged = []          # pinned host buffers whose copies are in flight
 
-    def _ws_bytes(self, cap: int) -> int:
+    def _ws_bytes(self, cap: int, spread: bool) -> int:
         """Collide workspace for WS_NODES nodes per pass; SSP-RK2 adds its two stage states."""
-        ws = self.plan.workspace_bytes(min(cap, WS_NODES))
+        nodes = min(cap, WS_NODES)
+        ws = self.plan.workspace_bytes(nodes) - (0 if spread else self.plan.spread_bytes(nodes))
         if self.scheme == "ssprk2":
             ws += 2 * (((cap * self.s * self.N ** 3 * 4) + 255) // 256 * 256)
         return ws
 
-    def bytes_for(self, cap: int) -> int:
+    def bytes_for(self, cap: int, spread: bool = True) -> int:
         if cap == 0:
             return 0
-        return cap * state_bytes(self.N, self.s) + self._ws_bytes(cap)
+        return cap * state_bytes(self.N, self.s) + self._ws_bytes(cap, spread)
+
+    def least_bytes_for(self, cap: int) -> int:
+        return self.bytes_for(cap, spread=False)
 
     def resize(self, cap: int, live: int) -> None:
         torch = self.torch
@@ -197,7 +204,7 @@ class DevicePool:
                 f[:live].copy_(self.f[:live])
             self.f = f
             self.Q = torch.empty(shape, dtype=torch.float32, device="cuda")
-            self.ws = torch.empty(self._ws_bytes(cap), dtype=torch.uint8, device="cuda")
+            self.ws = torch.empty(self._ws_bytes(cap, self.spread), dtype=torch.uint8, device="cuda")
         self.cap = cap
         self.peak_cap = max(self.peak_cap, cap)
 
@@ -248,7 +255,13 @@ class Pool:
         self.waiting = []          # admitted, not yet in a slot: (rid, staged payload)
         self.inflight = 0          # slots covered by the step in flight (0 = idle)
         self.held = 0              # bytes charged to the budget
+        self.alloc = 0             # bytes of the present allocation (held covers the next one too)
+        self.spread = True         # whether the next allocation has the optional part
         self.launches = 0
+
+    def bytes_for(self, cap: int, spread: bool) -> int:
+        least = getattr(self.dev, "least_bytes_for", None)
+        return self.dev.bytes_for(cap) if spread or least is None else least(cap)
 
 
 class Server:
@@ -281,16 +294,20 @@ class Server:
 
     # -- admission -------------------------------------------------------------------
     def try_admit(self, req: Request, staged) -> bool:
-        """Reserve the bytes the request's pool will hold with one more slot."""
+        """Reserve the bytes the request's pool will hold with one more slot, with the
+        optional part of the workspace if the budget has room for it."""
         pool = self.pool(req.key)
         need = len(pool.slots) + len(pool.waiting) + 1
-        target = pool.held
         if need > pool.dev.cap:
-            target = max(pool.held, pool.dev.bytes_for(grown_capacity(pool.dev.cap, need)))
-        if target > pool.held:
-            if not self.budget.try_take(target - pool.held):
+            # retirements before the pool grows may leave it at any smaller capacity
+            caps = sorted({grown_capacity(pool.dev.cap, n) for n in range(pool.dev.cap + 1, need + 1)})
+            for spread in (True, False):
+                target = max(pool.held, *(pool.bytes_for(c, spread) for c in caps))
+                if self.budget.try_take(target - pool.held):
+                    pool.held, pool.spread = target, spread
+                    break
+            else:
                 return False
-            pool.held = target
         pool.waiting.append((req.rid, staged))
         return True
 
@@ -326,17 +343,19 @@ class Server:
         if pool.waiting:
             need = len(pool.slots) + len(pool.waiting)
             if need > pool.dev.cap:
-                pool.dev.resize(grown_capacity(pool.dev.cap, need), len(pool.slots))
+                cap = grown_capacity(pool.dev.cap, need)
+                pool.dev.spread = pool.spread
+                pool.dev.resize(cap, len(pool.slots))
+                pool.alloc = pool.bytes_for(cap, pool.spread)
             for rid, staged in pool.waiting:
                 pool.dev.insert(len(pool.slots), staged)
                 pool.slots.append(rid)
                 pool.done.append(0)
             pool.waiting.clear()
             # retirements since the reservation may leave part of it unused
-            actual = pool.dev.bytes_for(pool.dev.cap)
-            if actual < pool.held:
-                self.budget.give(pool.held - actual)
-                pool.held = actual
+            if pool.alloc < pool.held:
+                self.budget.give(pool.held - pool.alloc)
+                pool.held = pool.alloc
         if pool.slots:
             pool.dev.launch(len(pool.slots))
             pool.inflight = len(pool.slots)
@@ -344,7 +363,7 @@ class Server:
         elif pool.held:
             pool.dev.resize(0, 0)
             self.budget.give(pool.held)
-            pool.held = 0
+            pool.held = pool.alloc = 0
         return retired
 
     def run(self, trace, staged=None, realtime=True, progress=None):

@@ -179,3 +179,92 @@ def test_grown_capacity_doubles_from_four():
     assert S.grown_capacity(4, 5) == 8
     assert S.grown_capacity(8, 33) == 64
     assert S.grown_capacity(16, 3) == 16
+
+
+class SizedPool(FakePool):
+    """A pool whose bytes per capacity are a table, with and without the optional part of its
+    workspace; it remembers what it holds."""
+
+    SPREAD = {4: 5000, 8: 9000, 16: 26000, 32: 20000}     # a capacity that needs more than the next
+    LEAST = {4: 2000, 8: 4000, 16: 8000, 32: 16000}
+
+    spread = True
+
+    def bytes_for(self, cap):
+        return self.SPREAD.get(cap, cap * 1000)
+
+    def least_bytes_for(self, cap):
+        return self.LEAST.get(cap, cap * 500)
+
+    def resize(self, cap, live):
+        super().resize(cap, live)
+        self.holds = 0 if cap == 0 else (self.bytes_for if self.spread else self.least_bytes_for)(cap)
+
+    def launch(self, n):
+        super().launch(n)
+        self.on_launch()
+
+
+class SizedBackend(FakeBackend):
+    def new_pool(self, key):
+        self.pools[key] = SizedPool(key, self.latency)
+        self.pools[key].holds = 0
+        self.pools[key].on_launch = self.check
+        return self.pools[key]
+
+
+def _one_pool(steps):
+    trace = S.make_trace(len(steps), 1e6, 3, steps=1, Ns=(4,))
+    for r, n in zip(trace, steps):
+        r.masses, r.steps = (1.0, 2.0), n
+    return trace
+
+
+@pytest.mark.parametrize("budget", [10 ** 6, 26000, 25999, 20000])
+def test_budget_covers_what_pools_hold_at_every_capacity(budget):
+    """Requests that retire between the reservation and the seating leave the pool at a
+    capacity other than the reserved one: the bytes charged are the bytes held all the same."""
+    backend = SizedBackend(latency=1)
+    srv = S.Server(backend=backend, budget_bytes=budget, keep_final=True)
+
+    def check():
+        for p in srv.pools.values():
+            assert p.dev.holds <= p.held
+        assert sum(p.dev.holds for p in srv.pools.values()) <= srv.budget.used <= budget
+
+    backend.check = check
+    trace = _one_pool([1] * 8 + [3] * 12)
+    staged, _ = srv.warm(trace)
+    order = sorted(trace, key=lambda r: r.t_arrive)
+    # eight requests in their last step; nine more reserve room for 17 (capacity 32) and are
+    # seated, after the eight have left, at 16
+    for r in order[:8]:
+        assert srv.try_admit(r, staged[r.rid])
+    reqs = {r.rid: r for r in trace}
+    (pool,) = srv.pools.values()
+    srv._service(pool, reqs, lambda: 0.0)
+    assert pool.dev.cap == 8 and pool.inflight == 8
+    took = 0
+    for r in order[8:17]:
+        took += srv.try_admit(r, staged[r.rid])
+    srv._service(pool, reqs, lambda: 0.0)
+    check()
+    assert pool.dev.holds == pool.held == srv.budget.used
+    assert took == 9 and pool.dev.cap == 16 and pool.spread == (budget >= 26000)
+
+
+def test_small_budget_serves_without_the_optional_part():
+    """A budget that fits a pool only without its optional part still serves every request."""
+    backend = SizedBackend(latency=1)
+    srv = S.Server(backend=backend, budget_bytes=SizedPool.LEAST[4], keep_final=True)
+    backend.check = lambda: None
+    trace = _one_pool([2] * 6)
+    staged, _ = srv.warm(trace)
+    srv.run(trace, staged, realtime=False)
+    for r in trace:
+        np.testing.assert_array_equal(r.final, _expected(r, staged[r.rid]))
+    assert srv.budget.used == 0 and srv.budget.peak <= SizedPool.LEAST[4]
+    # and one with room takes it again
+    srv = S.Server(backend=backend, budget_bytes=10 ** 6)
+    srv.try_admit(trace[0], staged[trace[0].rid])
+    assert srv.budget.used == SizedPool.SPREAD[4]
