@@ -120,6 +120,37 @@ def pair_tables(masses, L, N, M, n_rho, kernel, i, j, precision="f32", L_species
             "rho": np.array(rho[:]), "wrho": np.array(wrho[:]), "loss_by_k2": np.array(loss[:])}
 
 
+def _scratch(nbytes: int, optional: int, device, stream):
+    """A workspace of nbytes allocated on `stream`, or one without its optional bytes where the
+    device has no room for them."""
+    import torch
+    with torch.cuda.stream(stream):
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            if not optional:
+                raise
+        return torch.empty(nbytes - optional, dtype=torch.uint8, device=device)
+
+
+class _ScratchCache:
+    """One workspace per key, replaced when a call asks for more than it was made for.
+    optional: a function of no arguments that gives the optional bytes."""
+
+    def __init__(self):
+        self._held = {}
+
+    def get(self, key, nbytes: int, optional, device, stream):
+        ws, asked = self._held.get(key, (None, 0))
+        if ws is not None and ws.numel() >= nbytes:
+            return ws
+        least = nbytes - optional()
+        if ws is None or asked < nbytes or ws.numel() < least:
+            ws = _scratch(nbytes, nbytes - least, device, stream)
+            self._held[key] = ws, nbytes
+        return ws
+
+
 class CollisionPlan:
     """A precomputed collision problem on the current HIP device.
 
@@ -159,7 +190,7 @@ class CollisionPlan:
         check(self._lib.dgfs_plan_create(ctypes.byref(self._holder.problem), ctypes.byref(handle)),
               "dgfs_plan_create")
         self._plan = handle
-        self._ws = {}
+        self._ws = _ScratchCache()
 
     @property
     def dtype(self):
@@ -170,7 +201,7 @@ class CollisionPlan:
         if getattr(self, "_plan", None):
             self._lib.dgfs_plan_destroy(self._plan)
             self._plan = None
-        self._ws = {}
+        self._ws = _ScratchCache()
 
     def __del__(self):
         try:
@@ -194,18 +225,13 @@ class CollisionPlan:
         """A cached device workspace big enough for ``batch`` nodes in one pass, one per
         stream (calls on different streams may run concurrently, each needs its own).
         It is allocated on that stream, so the caching allocator orders any reuse of its
-        memory after the work queued there."""
+        memory after the work queued there.  workspace_bytes(batch) bytes, or without
+        spread_bytes(batch) of them where the device has no room for these."""
         import torch
         dev = torch.device(device or "cuda")
         st = stream if stream is not None else torch.cuda.current_stream(dev)
-        key = (str(dev), st.cuda_stream)
-        need = self.workspace_bytes(batch)
-        ws = self._ws.get(key)
-        if ws is None or ws.numel() < need:
-            with torch.cuda.stream(st):
-                ws = torch.empty(need, dtype=torch.uint8, device=dev)
-            self._ws[key] = ws
-        return ws
+        return self._ws.get((str(dev), st.cuda_stream), self.workspace_bytes(batch),
+                            lambda: self.spread_bytes(batch), dev, st)
 
     def _check_f(self, f):
         import torch
@@ -310,9 +336,8 @@ class CollisionPlan:
         if workspace is None:
             # allocated on the stream that uses it: freed on return, its memory is reused
             # only by work ordered after the queued steps
-            with torch.cuda.stream(st):
-                workspace = torch.empty(self.relax_workspace_bytes(max(f.shape[0], 1), scheme), dtype=torch.uint8,
-                                        device=f.device)
+            batch = max(f.shape[0], 1)
+            workspace = _scratch(self.relax_workspace_bytes(batch, scheme), self.spread_bytes(batch), f.device, st)
         check(self._lib.dgfs_relax(self._plan, c_void_p(f.data_ptr()), f.shape[0], float(dt), int(steps), code,
                                    c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
                                    c_void_p(st.cuda_stream)), "dgfs_relax")
@@ -342,7 +367,7 @@ class CollisionGroup:
         handle = c_void_p()
         check(self._lib.dgfs_group_create(arr, len(self.plans), ctypes.byref(handle)), "dgfs_group_create")
         self._group = handle
-        self._ws = {}
+        self._ws = _ScratchCache()
 
     def close(self):
         if getattr(self, "_group", None):
@@ -373,12 +398,9 @@ class CollisionGroup:
         if ws is None:
             # one cached workspace per calling stream, allocated on it (the group's own
             # streams fork from and join back to that stream)
-            key = st.cuda_stream
-            ws = self._ws.get(key)
-            if ws is None or ws.numel() < need:
-                with torch.cuda.stream(st):
-                    ws = torch.empty(need, dtype=torch.uint8, device=fs[0].device)
-                self._ws[key] = ws
+            ws = self._ws.get(st.cuda_stream, need,
+                              lambda: sum(p.spread_bytes(max(b, 1)) for p, b in zip(self.plans, batches)),
+                              fs[0].device, st)
         fa = (c_void_p * len(fs))(*[f.data_ptr() for f in fs])
         qa = (c_void_p * len(fs))(*[q.data_ptr() for q in outs])
         ba = (ctypes.c_int64 * len(fs))(*batches)
@@ -455,7 +477,7 @@ class Slab:
 
     def __init__(self, plan: "CollisionPlan", x0: float, x1: float, Ne: int, K: int, left: dict, right: dict,
                  collide: bool = True):
-        self.plan, self.Ne, self.K = plan, Ne, K
+        self.plan, self.Ne, self.K, self.collide = plan, Ne, K, bool(collide)
         self._lib = load()
         d = _lib.SlabDesc()
         d.x0, d.x1, d.Ne, d.K = float(x0), float(x1), int(Ne), int(K)
@@ -479,8 +501,8 @@ class Slab:
         code = {"euler": _lib.DGFS_EULER, "ssprk2": _lib.DGFS_SSPRK2}[scheme]
         st = stream if stream is not None else torch.cuda.current_stream(f.device)
         if workspace is None:
-            with torch.cuda.stream(st):   # see CollisionPlan.relax
-                workspace = torch.empty(self.workspace_bytes(scheme), dtype=torch.uint8, device=f.device)
+            optional = self.plan.spread_bytes(f.shape[0]) if self.collide else 0
+            workspace = _scratch(self.workspace_bytes(scheme), optional, f.device, st)   # see CollisionPlan.relax
         check(self._lib.dgfs_slab_step(self._slab, c_void_p(f.data_ptr()), float(dt), int(steps), code,
                                        c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
                                        c_void_p(st.cuda_stream)), "dgfs_slab_step")
