@@ -411,6 +411,7 @@ void build_tables(dgfs_plan& P, std::vector<char>& blob) {
         for (int d = 1; d < c.ndir; ++d)
             xs[size_t(c.dir_offset + d)] = P.sigma[3 * c.dirs[d]] == P.sigma[3 * c.dirs[d - 1]] ? 1 : 0;
     push_int(blob, P.off_xs, xs);
+    P.fresh_dirs = int(std::count(xs.begin(), xs.end(), 0));
 
     // ---------------- F tables per (class, target) and G tables per ordered pair
     const int K2 = P.K2;

@@ -297,20 +297,27 @@ __device__ __forceinline__ void x_sum_pipe(__amdgpu_buffer_rsrc_t rs, int vo, in
 // 3.  The others take the kept values back (the same values: nothing is rounded again)
 // instead of reading the spectrum and combining it anew.  It pays where the values find room in
 // registers or where the x-pass is most of the kernel.  Calls in us, without / with:
-//   VSS: FP32 N = 32 (96 nodes, argon-krypton) 8657 / 7888, N = 24 (40) 1243 / 1235, but
-//     N = 16 (100) 486 / 492 and N = 48 (5) 2401 / 2476; FP64 N = 32 (8) 2043 / 1891,
-//     N = 24 (20) 1588 / 1413, N = 16 (60) 780 / 758;
-//   VHS, N = 64: FP32 (2 nodes) 4554 / 4027, FP64 (1) 6016 / 5823;
-//   VHS, FP64: N = 32 (5, SSP-RK2 step) 1132 / 1100, N = 24 (60) 2038 / 2003, but
+//   VSS, M = 12: FP32 N = 32 (96 nodes) 8550 / 7790, but N = 24 (40) 1227 / 1220 with M = 6 691 /
+//     751, N = 16 (100) 486 / 492 and N = 48 (5) 2401 / 2476; FP64 N = 32 (8) 2030 / 1863, N = 24
+//     (20) 1575 / 1400, N = 16 (60) 771 / 749; M = 6: FP32 N = 32 (96) 4635 / 4595, FP64 N = 32
+//     1161 / 1150, N = 24 857 / 827, but N = 16 428 / 449;
+//   VHS, N = 64: FP32 (2 nodes) 3370 / 2966, FP64 (1) 4357 / 3790, M = 24 3575 / 2703, but M = 6
+//     FP32 487 / 516, FP64 589 / 667;
+//   VHS, FP64: N = 32 (16) 1672 / 1663, M = 24 (20) 1948 / 1680, M = 6 (16) 941 / 971; N = 24 (60)
+//     2018 / 1991, M = 24 1884 / 1640, M = 6 1121 / 1165; but
 //     N = 16 (200) 844 / 1140 and N = 48 (4) 3327 / 3662;
 //   VHS, FP32: N = 24 (63, DG) 3208 / 3641 and N = 16 (300) 583 / 722 (a wavefront per SIMD
 //     less); dealiased N = 32 (10) 1998 / 2460; the packed N = 48 form (7) 2296 / 3022 (two
 //     fields' values in private memory; in a place of the workspace per workgroup, 8 nodes
 //     of three species, 5.7 / 7.1 ms in the gain).
+// So some geometries keep them always, and some unless more than half of a plan's directions are
+// fresh (the octahedron's are: 2 of 3 and 3 of 6; the VSS classes of two directions, 5 of 6).
+enum { KEEP_NEVER = 0, KEEP_ALWAYS = 1, KEEP_BY_REUSE = 2 };
 template <typename T, int N, int MODE>
-constexpr bool keep_ok() {
-    if (MODE == GAIN_VSS) return N < 48 && (N > 16 || sizeof(T) == 8);
-    return MODE == GAIN_REAL && (N == 64 || (sizeof(T) == 8 && (N == 24 || N == 32)));
+constexpr int keep_rule() {
+    constexpr bool dbl = sizeof(T) == 8;
+    if (MODE == GAIN_VSS) return N == 32 || (N == 24 && dbl) ? KEEP_ALWAYS : N == 16 && dbl ? KEEP_BY_REUSE : KEEP_NEVER;
+    return MODE == GAIN_REAL && (N == 64 || (dbl && (N == 24 || N == 32))) ? KEEP_BY_REUSE : KEEP_NEVER;
 }
 template <int NP, typename T>
 __device__ __forceinline__ void keep_x(cx<T>* to, const cx<T>* from) {
@@ -895,7 +902,7 @@ __device__ __forceinline__ void store_partial(cx<T>* buf, cx<T>* Pq, int c) {
     }
 }
 
-template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, int MODE>
+template <typename T, int N, int CH, int CZ, int PIPE, bool PACK, int MODE, bool KEEP = false>
 __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArgs<T> a) {
     using K = GainK<T, N, CH, CZ>;
     constexpr bool CPLX = MODE == GAIN_COMPLEX || MODE == GAIN_VSS;  // the whole spectrum of a complex field is stored
@@ -994,7 +1001,6 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
     };
 
     // what at most this many rounds of the x-pass leave (keep_x)
-    constexpr bool KEEP = keep_ok<T, N, MODE>();
     constexpr int XR = KEEP ? (N * N / 2 + 2 + K::NT - 1) / K::NT : 1;
     cx<T> kept[2][XR][K::NP];
     auto direction = [&](int d, T* Sd) {
@@ -1770,7 +1776,13 @@ hipError_t run_slice(const dgfs_plan& p, const T* f, T* Q, int nb, Scratch ws, b
                 }
             }
         }
-        if (!split) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<dim3(gain_groups(nb, ipn)), block, 0, st>>>(ga);
+        constexpr int rule = keep_rule<T, N, MODE>();
+        const dim3 grid(gain_groups(nb, ipn));
+        const bool keep = rule == KEEP_ALWAYS || (rule == KEEP_BY_REUSE && 2 * p.fresh_dirs <= p.total_dirs);
+        if constexpr (rule != KEEP_NEVER)
+            if (!split && keep) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE, true><<<grid, block, 0, st>>>(ga);
+        if constexpr (rule != KEEP_ALWAYS)
+            if (!split && !keep) gain_kernel<T, N, CH, CZ, PIPE, PACK, MODE><<<grid, block, 0, st>>>(ga);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if constexpr (VSS) {

@@ -124,7 +124,7 @@ struct dgfs_plan {
     bool vss = false;           // some pair has alpha > 1: sigma-dependent kernel-mode tables
     std::vector<dgfs::PairParams> pair;  // [s*s]
     std::vector<dgfs::GainClass> classes;
-    int total_dirs = 0;
+    int total_dirs = 0, fresh_dirs = 0;  // fresh: with another sigma_x than the one before in its class
     int nftab = 0, ngtab = 0, K2 = 0;
     dgfs::SlotSet sum_slots, pair_slots;
 

@@ -65,3 +65,29 @@ def test_split_calls_equal_whole_ones(N, precision, tile, s, M, nrho, batches):
         assert torch.equal(plan.collide(ft[:batch], workspace=torch.empty(least, dtype=torch.uint8, device="cuda")), Q)
         for b in (0, batch - 1):
             assert torch.equal(plan.collide(ft[b:b + 1].contiguous())[0], Q[b]), b
+
+
+@pytest.mark.parametrize("N,precision,alpha,s,M", [
+    (64, "f32", 1.0, 1, 6), (64, "f64", 1.0, 1, 6), (64, "f64", 1.0, 1, 12), (32, "f64", 1.0, 2, 6), (24, "f64", 1.0, 2, 6),
+    (24, "f64", 1.0, 2, 12), (16, "f64", 1.4, 2, 6), (16, "f64", 1.4, 2, 12), (24, "f32", 1.4, 1, 12)])
+def test_x_transforms_kept_or_not(N, precision, alpha, s, M):
+    """Plans whose directions mostly share a sigma_x (M = 12) keep x-transforms in whole items,
+    those with more fresh directions (M = 6) do not: both against the oracle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import params as P
+    from paper_1903_03056_amd import CollisionPlan, vss_kernel
+    print(f"[case] kept x-transforms N={N} {precision} alpha={alpha} s={s} M={M}", flush=True)
+    masses, L, nrho, omega = (1.0, 2.0)[:s], 6.0, 2, 0.74
+    plan = CollisionPlan(masses, N, L, M, nrho, kernel=vss_kernel(masses, omega, alpha), precision=precision)
+    f = I.draw_bimaxwellian_batch(np.random.default_rng(71), 2, s, N, L, masses, noise=1e-2)
+    ft = torch.tensor(f, dtype=plan.dtype, device="cuda")
+    least = plan.workspace_bytes(2) - plan.spread_bytes(2)    # no room to split
+    Q = plan.collide(ft, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(plan.collide(ft), Q)
+    C = [[(omega, alpha, P.vss_prefactor(mi, mj, omega, alpha)) for mj in masses] for mi in masses]
+    ref = OS.collide(ft[1].double().cpu().numpy(), OS.Problem(masses=masses, L=L, N=N, M=M, nrho=nrho, kernel=C))
+    got = Q[1].double().cpu().numpy()
+    err = float(np.max(np.abs(got - ref).reshape(s, -1).max(1) / np.abs(ref).reshape(s, -1).max(1)))
+    print(f"relative L-inf {err:.3e}", flush=True)
+    assert err <= (1e-12 if precision == "f64" else 1e-5)
