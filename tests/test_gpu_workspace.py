@@ -121,3 +121,46 @@ def test_the_optional_part_is_bounded(N, M, nrho, precision, masses, batch, tile
     Q = plan.collide(f, workspace=_bytes(need + (256 << 20)))
     assert torch.equal(plan.collide(f, workspace=_bytes(need)), Q)
     assert torch.isfinite(Q).all() and float(Q.abs().max()) > 0
+
+
+@pytest.mark.parametrize("case", ["vhs", "grids", "vss", "dealiased", "matrix", "pairs", "relax"])
+@pytest.mark.parametrize("nodes", [1, 3])
+def test_slices_give_the_same_results(case, nodes):
+    """A workspace of `nodes` nodes without the optional part makes a batch of 7 run in slices
+    (the last one ragged for 3 nodes); one with it runs some slices split and others not."""
+    from paper_1903_03056_amd import vss_kernel
+    print(f"[case] slices {case} of {nodes}", flush=True)
+    if case == "grids":
+        plan = _plan(16, nrho=4, masses=(1.0, 20.0), L=(6.0, 2.0))
+    elif case == "vss":
+        plan = _plan(16, nrho=4, kernel=vss_kernel(MASSES, 0.74, 1.4))
+    elif case == "matrix":
+        plan = _plan(32, nrho=3)
+    else:
+        plan = _plan(16, nrho=4, dealias=case == "dealiased")
+    f = _state(plan, 7)
+    if case == "relax":
+        one = plan.relax_workspace_bytes(nodes) - plan.spread_bytes(nodes)
+        # the stage states of the whole batch, and the collide workspace of `nodes` nodes
+        states = 2 * ((7 - nodes) * plan.s * plan.N ** 3 * 4)
+        want = plan.relax(f.clone(), 0.01, 2)
+        run = lambda n: plan.relax(f.clone(), 0.01, 2, workspace=_bytes(states + n))
+        per = (plan.relax_workspace_bytes(20000) - plan.relax_workspace_bytes(10000)) // 10000 \
+            - 2 * plan.s * plan.N ** 3 * 4
+    else:
+        pairs = case == "pairs"
+        # the size counts the pair-resolved form's slots; a pass without them takes less
+        need = plan.workspace_bytes(nodes) - plan.spread_bytes(nodes)
+        per = _per_node(plan)
+        per_sum = (plan.relax_workspace_bytes(20000) - plan.relax_workspace_bytes(10000)) // 10000 \
+            - 2 * plan.s * plan.N ** 3 * 4
+        slack = plan.workspace_bytes(20000) - 20000 * per
+        one = need if pairs else per_sum * nodes + slack
+        per = per if pairs else per_sum
+        want = plan.collide(f, pairs=pairs)
+        run = lambda n: plan.collide(f, pairs=pairs, workspace=_bytes(n))
+    assert one < per * (nodes + 1)          # at most `nodes` nodes in a pass
+    assert torch.equal(run(one), want)
+    # room for the split's terms of fewer nodes than a slice has, and a little more
+    for extra in (plan.spread_bytes(1), per // 2, per + plan.spread_bytes(nodes) // 2):
+        assert torch.equal(run(one + extra), want)
