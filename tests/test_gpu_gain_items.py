@@ -91,3 +91,25 @@ def test_x_transforms_kept_or_not(N, precision, alpha, s, M):
     err = float(np.max(np.abs(got - ref).reshape(s, -1).max(1) / np.abs(ref).reshape(s, -1).max(1)))
     print(f"relative L-inf {err:.3e}", flush=True)
     assert err <= (1e-12 if precision == "f64" else 1e-5)
+
+
+def test_whole_fp64_items_at_n32():
+    """FP64 at N = 32 past the split (480 items): every node equals its result alone, which is
+    split, bit for bit, and the oracle's."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_03056_amd import CollisionPlan
+    masses, N, L, M, nrho, batch = (1.0, 2.0), 32, 6.0, 12, 8, 5
+    print(f"[case] whole items N={N} f64 M={M} batch {batch}", flush=True)
+    plan = CollisionPlan(masses, N, L, M, nrho, omega=0.74, precision="f64")
+    f = I.draw_bimaxwellian_batch(np.random.default_rng(73), batch, 2, N, L, masses, noise=1e-2)
+    ft = torch.tensor(f, device="cuda")
+    Q = plan.collide(ft)
+    for b in range(batch):
+        assert torch.equal(plan.collide(ft[b:b + 1].contiguous())[0], Q[b]), b
+    prob = OS.vhs_problem(masses, 0.74, L, N, M, nrho)
+    for b in (0, batch - 1):
+        ref = OS.collide(f[b], prob)
+        err = float(np.max(np.abs(Q[b].cpu().numpy() - ref).reshape(2, -1).max(1) / np.abs(ref).reshape(2, -1).max(1)))
+        print(f"relative L-inf {err:.3e}", flush=True)
+        assert err <= 1e-12
