@@ -907,7 +907,8 @@ __global__ __launch_bounds__((GainK<T, N, CH, CZ>::NT)) void gain_kernel(GainArg
     using K = GainK<T, N, CH, CZ>;
     constexpr bool CPLX = MODE == GAIN_COMPLEX || MODE == GAIN_VSS;  // the whole spectrum of a complex field is stored
     static_assert(!(PACK && CPLX), "the packed two-field form keeps only Re(A B)");
-    __shared__ cx<T> buf[K::LDS + ((PACK && pack_ok<T, N, CH, CZ>()) ? K::LINES : 0)];
+    // aligned for the 16-byte blocks of the Nyquist-plane sums
+    __shared__ alignas(16) cx<T> buf[K::LDS + ((PACK && pack_ok<T, N, CH, CZ>()) ? K::LINES : 0)];
     int b, item;
     // the items of a node: classes, or with GAIN_TERMS the directions of all classes
     const int nq = MODE == GAIN_TERMS ? a.nq : a.nrho;
