@@ -1423,11 +1423,12 @@ __device__ __forceinline__ void mirror_paired_row(int r, int& kxp, int& ky) {
 // 1.82 ms, for two 0.87), and so did FP64 (20 nodes at N = 32 10.6 ms; for one, NB = 2, 1.17).
 template <typename T, int CH>
 constexpr int vss_wpe() { return sizeof(T) == 8 ? 1 : CH <= 2 ? 3 : 2; }
-// Nodes per thread: one while that does not fill the chip's SIMDs with three wavefronts each
-// (FP64: one and a half), four from twice that many wavefronts of four (with one chunk, whose
-// registers are fewer, from two thirds of that: N = 16, 300 nodes of three species 2.87 ms a
-// call for two, 2.79 for four; 100 nodes of two 0.18 and 0.30 ms in the kernel), between them
-// two or three; fewer where the accumulators (NB x SMAX x CH) would not fit.
+// Nodes per thread: one while that does not fill the chip's 1024 SIMDs with three wavefronts each
+// (3072; FP64: 1536), four where a quarter of the one-node wavefronts are twice that many (6144)
+// or, with one chunk, whose registers are fewer, 2048 (N = 16, 300 nodes of three species, 2700:
+// 2.87 ms a call for two, 2.79 for four; 100 nodes of two, 900: 0.18 and 0.30 ms in the kernel),
+// between them three, or two with one chunk; fewer where the accumulators (NB x SMAX x CH) would
+// not fit.
 template <typename T, int CH, int SMAX>
 constexpr int vss_nb_max() { return sizeof(T) == 8 ? (CH <= 4 && SMAX == 2 ? 2 : 1) : CH >= 3 ? 1 : 8 / (CH * SMAX) >= 2 ? 4 : 2; }
 template <typename T, int CH, int SMAX>
