@@ -27,7 +27,7 @@ namespace dgfs {
 //               planes k_x, k_y or k_z = N/2 (the literal Nyquist reading), are reduced
 //               to those planes (sums with (-1)^x, (-1)^y, (-1)^z) and stored.
 // GAIN_TERMS    one direction of a GAIN_REAL item: its Re(A B) alone, stored unweighted in
-//               physical space for gain_sum_kernel (split_directions).
+//               physical space for gain_sum_kernel (split_rule in plan.hpp).
 enum { GAIN_REAL = 0, GAIN_COMPLEX = 1, GAIN_VSS = 2, GAIN_TERMS = 3 };
 
 // How the x-pass issues the loads of the next sub-sequence while it combines the current
